@@ -117,7 +117,7 @@ struct GemmParams {
 
 hipError_t launch_lut_gemm(const GemmParams& p, int ba, int bw, int cus, hipStream_t stream);
 // Rows [0, m_big) of an M x N layer run on the 256x256 kernel, the rest on the 128x128 kernel
-int64_t lut_gemm_big_rows(int64_t M, int64_t N, int cus);
+int64_t lut_gemm_big_rows(int64_t M, int64_t N, int64_t K, int cus);
 // K-splits of the 128x128 kernel on M x N outputs when a workspace is given (1: none), and the
 // K-steps per split (the last split may have fewer)
 int lut_gemm_small_splits(int64_t M, int64_t N, int64_t K, int cus, int* split_steps);

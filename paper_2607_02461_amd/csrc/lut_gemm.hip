@@ -17,6 +17,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device.h"
 
@@ -26,6 +27,10 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 128, BN = 128, BK = 64;
 constexpr int LDS_STRIDE = BK + 8;  // halves per tile row (padding against bank conflicts)
@@ -80,74 +85,148 @@ __device__ __forceinline__ void interleave(uint32_t lo, uint32_t hi, uint32_t& d
     d1 = __builtin_amdgcn_perm(hi, lo, 0x07030602u);  // [lo2 hi2 lo3 hi3]
 }
 
-// 2- and 3-bit groups: every level is in the table
+// Group g (codes 8g .. 8g+7) of 32 packed codes (4*BITS bytes, LSB-first) -> four bf16x2 words in
+// canonical slot order, in eight pieces (0-3 the even codes, 4-7 the odd ones, with a few exceptions)
+// that the kernels place between their MFMAs: with the decode in one lump behind four MFMAs the
+// large kernel runs 5% slower.  The empty asm on the code word pins the decode at its use: otherwise
+// the compiler starts it right after the codes' load, which then has to complete a whole K-step early.
 template <int BITS>
-__device__ __forceinline__ void decode8_small(const Codes<BITS>& w, int g, const ByteTables& t, uint32_t (&out)[4]) {
-    uint32_t lo, hi;
-    uint32_t ce, co;  // codes k0 k2 k4 k6 and k1 k3 k5 k7, one per byte
-    if constexpr (BITS == 2) {
-        uint32_t xw = w[g >> 1];
-        asm volatile("" : "+v"(xw));  // as in decode8: keep the decode at its use
-        const uint32_t x = xw >> (16 * (g & 1));             // 16 bits, code j at bits 2j
-        const uint32_t e = x & 0x3333u, o = (x >> 2) & 0x3333u;  // nibble i holds k2i (k2i+1)
-        ce = __builtin_amdgcn_perm(e >> 4, e, 0x05010400u) & 0x03030303u;
-        co = __builtin_amdgcn_perm(o >> 4, o, 0x05010400u) & 0x03030303u;
-    } else {
-        static_assert(BITS == 3, "bits");
-        const int bit = 24 * g;                               // 24 bits, code j at bits 3j
-        uint32_t x = bit == 0 ? w[0] : bit == 24 ? (w[0] >> 24) | (w[1] << 8)
-                   : bit == 48 ? (w[1] >> 16) | (w[2] << 16) : w[2] >> 8;
-        asm volatile("" : "+v"(x));  // as in decode8: keep the decode at its use
-        ce = (x & 7u) | (((x >> 6) & 7u) << 8) | (((x >> 12) & 7u) << 16) | (((x >> 18) & 7u) << 24);
-        co = ((x >> 3) & 7u) | (((x >> 9) & 7u) << 8) | (((x >> 15) & 7u) << 16) | (((x >> 21) & 7u) << 24);
+struct Decode8 {
+    uint32_t x, lo, hi, out[4];
+
+    template <int P>
+    __device__ __forceinline__ void piece(const Codes<BITS>& w, int g, const ByteTables& t) {
+        if constexpr (BITS == 4) {
+            // nibble j of x is the label of code k_j: bits 0-2 index the magnitude table, bit 3 (the
+            // sign) becomes bit 7 of the high byte, where bf16 keeps its sign
+            if constexpr (P == 0) {
+                x = w[g];
+                asm volatile("" : "+v"(x));
+                lookup_bytes(x & 0x07070707u, t, lo, hi);          // k0 k2 k4 k6
+            } else if constexpr (P == 1) {
+                hi |= (x << 4) & 0x80808080u;
+            } else if constexpr (P == 2) {
+                interleave(lo, hi, out[0], out[1]);
+            } else if constexpr (P == 3) {
+                lookup_bytes((x >> 4) & 0x07070707u, t, lo, hi);   // k1 k3 k5 k7
+            } else if constexpr (P == 4) {
+                hi |= x & 0x80808080u;
+            } else if constexpr (P == 5) {
+                interleave(lo, hi, out[2], out[3]);
+            }
+        } else if constexpr (BITS == 3) {
+            // 24 bits, code j at bits 3j.  Four fields 6 bits apart move 2, 4 and 6 bits up to the bytes
+            // of a word in two steps (fields 2, 3 by four, then fields 1, 3 by two)
+            if constexpr (P == 0) {
+                const int bit = 24 * g;
+                x = bit == 0 ? w[0] : bit == 24 ? __builtin_amdgcn_alignbit(w[1], w[0], 24)
+                  : bit == 48 ? __builtin_amdgcn_alignbit(w[2], w[1], 16) : w[2] >> 8;
+                asm volatile("" : "+v"(x));
+                lo = spread6(x);
+            } else if constexpr (P == 1) {
+                lookup_bytes(lo, t, lo, hi);
+            } else if constexpr (P == 2) {
+                interleave(lo, hi, out[0], out[1]);
+            } else if constexpr (P == 4) {
+                lo = spread6(x >> 3);
+            } else if constexpr (P == 5) {
+                lookup_bytes(lo, t, lo, hi);
+            } else if constexpr (P == 6) {
+                interleave(lo, hi, out[2], out[3]);
+            }
+        } else {
+            static_assert(BITS == 2, "bits");
+            if constexpr (P == 0) {
+                uint32_t xw = w[g >> 1];
+                asm volatile("" : "+v"(xw));
+                x = xw >> (16 * (g & 1));                        // 16 bits, code j at bits 2j
+                const uint32_t e = x & 0x3333u;                  // nibble i holds k2i
+                lo = __builtin_amdgcn_perm(e >> 4, e, 0x05010400u) & 0x03030303u;
+            } else if constexpr (P == 1) {
+                lookup_bytes(lo, t, lo, hi);
+            } else if constexpr (P == 2) {
+                interleave(lo, hi, out[0], out[1]);
+            } else if constexpr (P == 4) {
+                const uint32_t o = (x >> 2) & 0x3333u;           // nibble i holds k2i+1
+                lo = __builtin_amdgcn_perm(o >> 4, o, 0x05010400u) & 0x03030303u;
+            } else if constexpr (P == 5) {
+                lookup_bytes(lo, t, lo, hi);
+            } else if constexpr (P == 6) {
+                interleave(lo, hi, out[2], out[3]);
+            }
+        }
     }
-    lookup_bytes(ce, t, lo, hi);
-    interleave(lo, hi, out[0], out[1]);
-    lookup_bytes(co, t, lo, hi);
-    interleave(lo, hi, out[2], out[3]);
-}
+
+    static __device__ __forceinline__ uint32_t spread6(uint32_t v) {
+        v = (v & 0x00000FFFu) | ((v << 4) & 0xFFFFF000u);        // fields at 0, 6, 16, 22
+        return ((v & 0x00FF00FFu) | ((v << 2) & 0xFF00FF00u)) & 0x07070707u;
+    }
+};
 
 // 6-bit groups: 64 levels are too many for byte permutes, so the bf16 levels sit in a 64-entry
 // LDS table with a 4-byte stride; every entry has its own bank, so a wave's 64 lookups never
 // conflict (equal codes broadcast).
-__device__ __forceinline__ void decode8_lds6(const Codes<6>& w, int g, const uint32_t* tab, uint32_t (&out)[4]) {
-    // group g covers bits 48g .. 48g+47 of the 192-bit stream (selects, not an indexed load from
-    // the register array)
-    uint32_t lo = g == 0 ? w[0] : g == 1 ? w[1] : g == 2 ? w[3] : w[4];
-    uint32_t hi = g == 0 ? w[1] : g == 1 ? w[2] : g == 2 ? w[4] : w[5];
-    asm volatile("" : "+v"(lo), "+v"(hi));  // as in decode8: keep the decode at its use
-    const uint64_t x = (((uint64_t)hi << 32) | lo) >> ((g & 1) * 16);
-    uint32_t v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = tab[(uint32_t)(x >> (6 * j)) & 63u];
-    out[0] = v[0] | (v[2] << 16);
-    out[1] = v[4] | (v[6] << 16);
-    out[2] = v[1] | (v[3] << 16);
-    out[3] = v[5] | (v[7] << 16);
+template <>
+struct Decode8<6> {
+    uint32_t lo, hi, v[8], out[4];
+    const uint32_t* tab;
+
+    template <int P>
+    __device__ __forceinline__ void piece(const Codes<6>& w, int g, const ByteTables&) {
+        if constexpr (P == 0) {
+            // group g covers bits 48g .. 48g+47 of the 192-bit stream (selects, not an indexed load
+            // from the register array)
+            lo = g == 0 ? w[0] : g == 1 ? w[1] : g == 2 ? w[3] : w[4];
+            hi = g == 0 ? w[1] : g == 1 ? w[2] : g == 2 ? w[4] : w[5];
+            asm volatile("" : "+v"(lo), "+v"(hi));
+        }
+        if constexpr (P < 4) {
+            const uint64_t x = (((uint64_t)hi << 32) | lo) >> ((g & 1) * 16);
+            v[2 * P] = tab[(uint32_t)(x >> (12 * P)) & 63u];
+            v[2 * P + 1] = tab[(uint32_t)(x >> (12 * P + 6)) & 63u];
+        } else if constexpr (P == 4) {
+            out[0] = v[0] | (v[2] << 16);
+        } else if constexpr (P == 5) {
+            out[1] = v[4] | (v[6] << 16);
+        } else if constexpr (P == 6) {
+            out[2] = v[1] | (v[3] << 16);
+        } else {
+            out[3] = v[5] | (v[7] << 16);
+        }
+    }
+};
+
+template <int P>
+using Piece = std::integral_constant<int, P>;
+
+// Pieces 2Q and 2Q + 1; all eight
+template <int Q, int BITS>
+__device__ __forceinline__ void two_pieces(Decode8<BITS>& d, const Codes<BITS>& w, int g, const ByteTables& t) {
+    d.template piece<2 * Q>(w, g, t);
+    d.template piece<2 * Q + 1>(w, g, t);
+}
+template <int BITS>
+__device__ __forceinline__ uint4 decode_all(Decode8<BITS>& d, const Codes<BITS>& w, int g, const ByteTables& t) {
+    two_pieces<0>(d, w, g, t);
+    two_pieces<1>(d, w, g, t);
+    two_pieces<2>(d, w, g, t);
+    two_pieces<3>(d, w, g, t);
+    return make_uint4(d.out[0], d.out[1], d.out[2], d.out[3]);
 }
 
-// Group g (codes 8g .. 8g+7) of 32 packed codes (4*BITS bytes, LSB-first) -> four bf16x2 words
-// in canonical slot order.
-template <int BITS>
-__device__ __forceinline__ void decode8(const Codes<BITS>& w, int g, const ByteTables& t, const uint32_t* tab6,
-                                        uint32_t (&out)[4]) {
-    uint32_t lo, hi;
-    if constexpr (BITS == 6) {
-        decode8_lds6(w, g, tab6, out);
-    } else if constexpr (BITS == 4) {
-        // nibble j of x is the label of code k_j: bits 0-2 index the magnitude table, bit 3 (the
-        // sign) becomes bit 7 of the high byte, where bf16 keeps its sign.  The empty asm pins the
-        // decode here: otherwise the compiler starts it right after the codes' load, which then
-        // has to complete a whole K-step early.
-        uint32_t x = w[g];
-        asm volatile("" : "+v"(x));
-        lookup_bytes(x & 0x07070707u, t, lo, hi);                  // k0 k2 k4 k6
-        interleave(lo, hi | ((x << 4) & 0x80808080u), out[0], out[1]);
-        lookup_bytes((x >> 4) & 0x07070707u, t, lo, hi);           // k1 k3 k5 k7
-        interleave(lo, hi | (x & 0x80808080u), out[2], out[3]);
-    } else {
-        decode8_small<BITS>(w, g, t, out);
-    }
+// c += b a^T for 16 rows of b and of a, 32 deep.  Written out so that the accumulator stays in its
+// registers: the compiler gives the intrinsic's result a fresh quad, and with 32 quads of
+// accumulators in 256 registers it then spills (2 to 22 registers; at 6-bit codes the large kernel ran
+// at 0.79 of the rate).  The compiler's hazard tracking does not look inside asm: the fragments come
+// from LDS loads (waited for by counter) and nothing but these MFMAs writes the accumulators between
+// their zeroing, which a barrier separates from the first use, and mfma_done().
+__device__ __forceinline__ void mfma16(floatx4& c, const bf16x8& b, const bf16x8& a) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(b), "v"(a));
+}
+
+// The wait states between the last MFMAs and the first other use of their results.
+__device__ __forceinline__ void mfma_done(floatx4 (&c)[4]) {
+    asm volatile("s_nop 15" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
 }
 
 template <int BITS>
@@ -165,6 +244,32 @@ __device__ __forceinline__ void load_codes32(const uint8_t* src, Codes<BITS>& w)
     } else {
         const uint32_t* s = (const uint32_t*)src;
         w[0] = s[0]; w[1] = s[1]; w[2] = s[2]; w[3] = 0;
+    }
+}
+
+// The code rows of a block tile as a buffer resource, and the same load through it: the tile's base
+// and the K-step's offset are scalar, so a load takes one address register per lane and no address
+// arithmetic.  Offsets are 32-bit: the caller keeps a tile's rows below 4 GiB.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t code_buffer(const uint8_t* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00027000);
+}
+
+template <int BITS>
+__device__ __forceinline__ void load_codes32(__amdgpu_buffer_rsrc_t buf, uint32_t voff, uint32_t soff, Codes<BITS>& w) {
+    if constexpr (BITS == 4) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(buf, voff, soff, 0);
+        w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+    } else if constexpr (BITS == 6) {
+        const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(buf, voff, soff, 0);
+        const u32x2 b = __builtin_amdgcn_raw_buffer_load_b64(buf, voff + 8, soff, 0);
+        const u32x2 c = __builtin_amdgcn_raw_buffer_load_b64(buf, voff + 16, soff, 0);
+        w[0] = a.x; w[1] = a.y; w[2] = b.x; w[3] = b.y; w[4] = c.x; w[5] = c.y;
+    } else if constexpr (BITS == 2) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(buf, voff, soff, 0);
+        w[0] = v.x; w[1] = v.y; w[2] = 0; w[3] = 0;
+    } else {
+        const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(buf, voff, soff, 0);
+        w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = 0;
     }
 }
 
@@ -219,6 +324,39 @@ __device__ __forceinline__ void store_one(const GemmParams& p, int64_t row, int6
         ((float*)p.Y)[row * p.ldy + col] = v;
 }
 
+// bf16 r' and bias (zero without one) of columns c .. c+3, zero past the last column
+__device__ __forceinline__ void load_columns(const GemmParams& p, int64_t c, uint2& rw, uint2& bias) {
+    if (c + 3 < p.N && p.vec4) {
+        rw = *(const uint2*)(p.wn + c);
+        bias = p.bias ? *(const uint2*)(p.bias + c) : make_uint2(0u, 0u);
+    } else {
+        uint16_t v[4], w[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            v[r] = c + r < p.N ? p.wn[c + r] : (uint16_t)0;
+            w[r] = p.bias && c + r < p.N ? p.bias[c + r] : (uint16_t)0;
+        }
+        rw = make_uint2(v[0] | ((uint32_t)v[1] << 16), v[2] | ((uint32_t)v[3] << 16));
+        bias = make_uint2(w[0] | ((uint32_t)w[1] << 16), w[2] | ((uint32_t)w[3] << 16));
+    }
+}
+
+// finished outputs of columns c .. c+3 of a row, as one vector where the layout allows it
+__device__ __forceinline__ void store_four(const GemmParams& p, int64_t row, int64_t c, const floatx4& v) {
+    const bool full = c + 3 < p.N && p.vec4;
+    if (full && p.out_bf16) {
+        *(uint2*)((uint16_t*)p.Y + row * p.ldy + c) =
+            make_uint2(f32_to_bf16_rne(v[0]) | (f32_to_bf16_rne(v[1]) << 16),
+                       f32_to_bf16_rne(v[2]) | (f32_to_bf16_rne(v[3]) << 16));
+    } else if (full) {
+        *(float4*)((float*)p.Y + row * p.ldy + c) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (c + r < p.N) store_one(p, row, c + r, v[r]);
+    }
+}
+
 // SPLIT: workgroup z of a K-split contracts K-steps z*steps .. (z+1)*steps - 1 (the last split
 // fewer) and stores its raw sums to p.ws[z][M][N]; lut_gemm_reduce applies the epilogue.
 //
@@ -241,9 +379,12 @@ __global__ __launch_bounds__(256) void lut_gemm_kernel(GemmParams p) {
     const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
     const ByteTables ta = make_tables<BA>(p.lut_a);
     const ByteTables tw = make_tables<BW>(p.lut_w);
+    Decode8<BA> da;
+    Decode8<BW> db;
     if constexpr (BA == 6) {
         if (tid < 64) tab6[tid] = p.lut_a[tid];
         __syncthreads();
+        da.tab = tab6;
     }
 
     // this thread decodes 32 codes of one A row and 32 codes of one B row per K-step
@@ -270,11 +411,8 @@ __global__ __launch_bounds__(256) void lut_gemm_kernel(GemmParams p) {
     const __bf16* const b_frag0 = slds + SMALL_TILE + (wn * 64 + (lane & 31)) * LDS_STRIDE + (lane >> 5) * 8;
 
     auto decode_group = [&](int stage, int g, const Codes<BA>& ca, const Codes<BW>& cb) {
-        uint32_t da[4], db[4];
-        decode8<BA>(ca, g, ta, tab6, da);
-        decode8<BW>(cb, g, tw, nullptr, db);
-        *(uint4*)(a_dst0 + stage + 8 * g) = make_uint4(da[0], da[1], da[2], da[3]);
-        *(uint4*)(a_dst0 + stage + SMALL_TILE + 8 * g) = make_uint4(db[0], db[1], db[2], db[3]);
+        *(uint4*)(a_dst0 + stage + 8 * g) = decode_all(da, ca, g, ta);
+        *(uint4*)(a_dst0 + stage + SMALL_TILE + 8 * g) = decode_all(db, cb, g, tw);
     };
 
     // a ring of RING code register sets: set u holds the codes of the steps congruent to u, so
@@ -527,20 +665,33 @@ __global__ __launch_bounds__(256) void lut_gemm_kernel(GemmParams p) {
 
 // ------------------------------------------------------------------------------------------
 // Large-problem kernel: 256x256 block tiles, K-step 64, eight waves of 128x64 each.  Every code
-// of a block tile is decoded once per K-step into a double-buffered bf16 tile in LDS (147 KB),
+// of a block tile is decoded once per K-step into a double-buffered bf16 tile in LDS (128 KB),
 // which halves the decodes per flop of the 128x128 kernel.  While the matrix cores work on step
-// s, each wave decodes step s+1 into the other stage, a quarter per 16-wide k slice, and the
-// codes of steps s+2 and s+3 are in flight.  Block tiles are visited so that the
-// workgroups resident on one XCD (round-robin dispatch) share A and B panels in that XCD's L2.
+// s, each wave decodes step s+1 into the other stage, and the codes of steps s+2 and s+3 are in
+// flight.  Block tiles are visited so that the workgroups resident on one XCD (round-robin
+// dispatch) share A and B panels in that XCD's L2.
+//
+// The kernel is bound by power: under its load the clock settles at 1.8-1.9 GHz of 2.4, so what
+// counts is the energy of a step.  Hence v_mfma_f32_16x16x32_bf16 and not the 32x32x16 form: per
+// product it moves a quarter of the accumulator bytes and twice the operand bytes, 0.5 against
+// 0.62 bytes per multiply-add of register traffic, and a register-only loop on 4-bit Lloyd-Max
+// levels runs at 2035 against 1800 TFLOP/s with it (2420 and 2460 on constant operands, where
+// power does not bind).  Measured with it on 33272 x 5120 outputs, K = 13824, W4A4: 3.82 -> 3.50 ms
+// (1233 -> 1346 TFLOP/s); 9216 x 9216, K = 3072, W2A4: 480 -> 432 us; 33272 x 13824, K = 5120, W4A6
+// with GELU: 4.78 -> 4.56 ms.  Of that, the chunk swizzle below is 1.6% (padded rows of 144 bytes
+// conflict two ways under the 16-row fragment reads) and walking the B fragments back and forth,
+// so that neighbouring MFMAs share an operand, 1.3%.  The same loop without its decode runs 10%
+// faster, without its LDS writes 7%.
 constexpr int BM2 = 256, BN2 = 256, BK2 = 64;
-constexpr int LDS2_STRIDE = BK2 + 8;                  // halves per tile row; 144 B keeps 16-byte
-                                                      // fragment reads of 16 rows conflict-free
-constexpr int LDS2_TILE = BM2 * LDS2_STRIDE;          // halves per operand tile
+constexpr uint32_t LDS2_TILE = BM2 * BK2 * 2;          // bytes per operand tile (rows of 128)
+constexpr uint32_t LDS2_BYTES = 8 * 64 * 68 * 4;       // the epilogue's regions: more than two stages
+static_assert(LDS2_BYTES >= 4 * LDS2_TILE, "the stages fit");
+constexpr int64_t MAX_K2 = (int64_t)1 << 24;           // 256 rows of 6-bit codes stay below 4 GiB
 constexpr int GROUP_M = 8;                            // block rows per L2 group
 
 template <int BA, int BW>
 __global__ __launch_bounds__(512, 2) void lut_gemm_big(GemmParams p, int ntm, int ntn, int per_xcd) {
-    extern __shared__ __align__(16) __bf16 lds[];  // [stage][A, B][256][72]
+    extern __shared__ __align__(16) unsigned char lds[];  // A, B: [stage][256][64] bf16, chunks swizzled
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 2, wn = wave & 3;
 
@@ -558,184 +709,200 @@ __global__ __launch_bounds__(512, 2) void lut_gemm_big(GemmParams p, int ntm, in
 
     const ByteTables ta = make_tables<BA>(p.lut_a);
     const ByteTables tw = make_tables<BW>(p.lut_w);
-    uint32_t* const tab6 = (uint32_t*)(lds + 2 * 2 * LDS2_TILE);  // 6-bit levels, after the tiles
+    Decode8<BA> da;
+    Decode8<BW> db;
     if constexpr (BA == 6) {
+        uint32_t* const tab6 = (uint32_t*)(lds + LDS2_BYTES);  // 6-bit levels, after the tiles
         if (tid < 64) tab6[tid] = p.lut_a[tid];
         __syncthreads();
+        da.tab = tab6;
     }
 
     // this thread decodes 32 codes of one A row and 32 codes of one B row per K-step
     const int lr = tid >> 1, lh = tid & 1;
     const int64_t arow = min(m0 + lr, p.M - 1), brow = min(n0 + lr, p.N - 1);
-    const uint8_t* asrc = p.xc + arow * ((int64_t)p.K * BA / 8) + lh * 4 * BA;
-    const uint8_t* bsrc = p.wc + brow * ((int64_t)p.K * BW / 8) + lh * 4 * BW;
+    const uint32_t a_row = (uint32_t)p.K / 8 * BA, b_row = (uint32_t)p.K / 8 * BW;  // bytes (K <= MAX_K2)
+    const __amdgpu_buffer_rsrc_t abuf = code_buffer(p.xc + m0 * a_row, (uint32_t)min((int64_t)BM2, p.M - m0) * a_row);
+    const __amdgpu_buffer_rsrc_t bbuf = code_buffer(p.wc + n0 * b_row, (uint32_t)min((int64_t)BN2, p.N - n0) * b_row);
+    const uint32_t aoff = (uint32_t)(arow - m0) * a_row + lh * 4 * BA;
+    const uint32_t boff = (uint32_t)(brow - n0) * b_row + lh * 4 * BW;
 
-    floatx16 acc[4][2];
+    floatx4 acc[8][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
     const int nk = p.K / BK2;
-    const int64_t astep = BK2 * BA / 8, bstep = BK2 * BW / 8;
-    __bf16* const a_dst0 = lds + lr * LDS2_STRIDE + lh * 32;  // this thread's decode slots, stage 0
-    const __bf16* const a_frag0 = lds + (wm * 128 + (lane & 31)) * LDS2_STRIDE + (lane >> 5) * 8;
-    const __bf16* const b_frag0 = lds + LDS2_TILE + (wn * 64 + (lane & 31)) * LDS2_STRIDE + (lane >> 5) * 8;
-    constexpr int STAGE = 2 * LDS2_TILE;
-
-    Codes<BA> wa, xa, ya;
-    Codes<BW> wb, xb, yb;
-    load_codes32<BA>(asrc, wa);
-    load_codes32<BW>(bsrc, wb);
+    const int astep = BK2 * BA / 8, bstep = BK2 * BW / 8;
+    // A tile row is 128 bytes; its 16-byte chunk c sits at chunk c ^ (row & 7).  A fragment read (16
+    // rows, four chunks of each) and a decode's write (32 rows, two chunks of each) are then free of
+    // bank conflicts.  The two stages of an operand are neighbours (an immediate offset).
+    uint32_t adst[4], bdst[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-        uint32_t da[4], db[4];
-        decode8<BA>(wa, g, ta, tab6, da);
-        decode8<BW>(wb, g, tw, nullptr, db);
-        *(uint4*)(a_dst0 + 8 * g) = make_uint4(da[0], da[1], da[2], da[3]);
-        *(uint4*)(a_dst0 + LDS2_TILE + 8 * g) = make_uint4(db[0], db[1], db[2], db[3]);
+        adst[g] = lr * 128 + (((lh * 4) ^ (lr & 7)) ^ g) * 16;
+        bdst[g] = adst[g] + 2 * LDS2_TILE;
+    }
+    const uint32_t fswz = (uint32_t)((lane >> 4) ^ (lane & 7)) * 16;
+    const uint32_t afrag = (wm * 128 + (lane & 15)) * 128 + fswz;
+    const uint32_t bfrag = (wn * 64 + (lane & 15)) * 128 + fswz + 2 * LDS2_TILE;
+
+    // four code register sets: set u holds the codes of the steps congruent to u
+    Codes<BA> sa[4];
+    Codes<BW> sb[4];
+    load_codes32<BA>(abuf, aoff, 0, sa[0]);
+    load_codes32<BW>(bbuf, boff, 0, sb[0]);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        *(uint4*)(lds + adst[g]) = decode_all(da, sa[0], g, ta);
+        *(uint4*)(lds + bdst[g]) = decode_all(db, sb[0], g, tw);
     }
     {
-        const int64_t s1 = nk > 1 ? 1 : 0, s2 = nk > 2 ? 2 : nk - 1;
-        load_codes32<BA>(asrc + s1 * astep, wa);
-        load_codes32<BW>(bsrc + s1 * bstep, wb);
-        load_codes32<BA>(asrc + s2 * astep, ya);
-        load_codes32<BW>(bsrc + s2 * bstep, yb);
+        const int s1 = nk > 1 ? 1 : 0, s2 = nk > 2 ? 2 : nk - 1;
+        load_codes32<BA>(abuf, aoff, s1 * astep, sa[1]);
+        load_codes32<BA>(abuf, aoff, s2 * astep, sa[2]);
+        load_codes32<BW>(bbuf, boff, s1 * bstep, sb[1]);
+        load_codes32<BW>(bbuf, boff, s2 * bstep, sb[2]);
     }
     __syncthreads();
 
-    // fragments of one 16-wide k slice of a stage
-    bf16x8 a[2][4], b[2][2];
-    auto read_frags = [&](int stage, int kk, bf16x8 (&af)[4], bf16x8 (&bf)[2]) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) af[i] = *(const bf16x8*)(a_frag0 + stage + i * 32 * LDS2_STRIDE + kk * 16);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) bf[j] = *(const bf16x8*)(b_frag0 + stage + j * 32 * LDS2_STRIDE + kk * 16);
+    // A K-step is sixteen groups of 4 MFMAs: group q contracts the 32-deep k slice q / 8 of A fragment
+    // q % 8 with the slice's four B fragments.  A fragments are read three groups ahead.
+    bf16x8 a[4], b[2][4];
+    auto read_a = [&](uint32_t stage, int q) {
+        a[q & 3] = *(const bf16x8*)(lds + (afrag ^ (64 * (q >> 3))) + stage + (q & 7) * 2048);
     };
-    auto decode_group = [&](int nxt, int g, const Codes<BA>& ca, const Codes<BW>& cb) {
-        uint32_t da[4], db[4];
-        decode8<BA>(ca, g, ta, tab6, da);
-        decode8<BW>(cb, g, tw, nullptr, db);
-        *(uint4*)(a_dst0 + nxt + 8 * g) = make_uint4(da[0], da[1], da[2], da[3]);
-        *(uint4*)(a_dst0 + nxt + LDS2_TILE + 8 * g) = make_uint4(db[0], db[1], db[2], db[3]);
+    auto read_b = [&](uint32_t stage, int slice, int j) {
+        b[slice][j] = *(const bf16x8*)(lds + (bfrag ^ (64 * slice)) + stage + j * 2048);
     };
-    read_frags(0, 0, a[0], b[0]);
+    read_a(0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) read_b(0, 0, j);
+    read_a(0, 1);
+    read_a(0, 2);
 
-    // One K-step in four 16-wide slices.  Slices 0-2 decode the codes of step s+1 (ca, cb) into
-    // the other stage while their MFMAs run; then one barrier makes that stage complete and
-    // retires every read of this step's stage, so slice 3 can already fetch the next step's
-    // first fragments while its MFMAs run.  The codes of step s+3 load into (na, nb), so each
-    // load has two K-steps to land.  Three register sets rotate: the loop below is unrolled by
-    // three so that they change roles instead of being copied (a copy would wait for the load).
-    auto kstep = [&](int s, const Codes<BA>& ca, const Codes<BW>& cb, Codes<BA>& na, Codes<BW>& nb) {
-        // the last steps re-load the final step's codes; they are never used
-        const int64_t s2 = min(s + 3, nk - 1);
-        load_codes32<BA>(asrc + s2 * astep, na);
-        load_codes32<BW>(bsrc + s2 * bstep, nb);
+    // Groups 0-11 decode the codes of step s+1 into the other stage, a piece behind every MFMA; then
+    // one barrier makes that stage complete and retires every read of this step's stage, so groups
+    // 13-15 can already fetch the next step's first fragments while their MFMAs run.  Even steps load
+    // the codes of steps s+3 and s+4 (64 bytes of each row in one go: 1.3-2% over one step at a time,
+    // a quarter fewer requests to the L2), so each load has two K-steps to land.
+    auto kstep = [&](auto u_tag, int s) {
+        constexpr int U = decltype(u_tag)::value;
+        const Codes<BA>& ca = sa[(U + 1) & 3];
+        const Codes<BW>& cb = sb[(U + 1) & 3];
+        if constexpr (U % 2 == 0) {
+            // the last steps re-load the final step's codes; they are never used
+            const int s3 = min(s + 3, nk - 1), s4 = min(s + 4, nk - 1);
+            load_codes32<BA>(abuf, aoff, s3 * astep, sa[(U + 3) & 3]);
+            load_codes32<BA>(abuf, aoff, s4 * astep, sa[U]);
+            load_codes32<BW>(bbuf, boff, s3 * bstep, sb[(U + 3) & 3]);
+            load_codes32<BW>(bbuf, boff, s4 * bstep, sb[U]);
+        }
         __builtin_amdgcn_sched_barrier(0);
 
-        const int cur = (s & 1) * STAGE, nxt = STAGE - cur;
+        constexpr uint32_t cur = (U & 1) * LDS2_TILE, nxt = LDS2_TILE - cur;
 #pragma unroll
-        for (int kk = 0; kk < BK2 / 16; ++kk) {
-            const int f = kk & 1;
-            if (kk == 3) __syncthreads();
-            // next slice's fragments; after the barrier, the next step's first slice (on the final
-            // step a refilled stage nobody uses)
-            if (kk < 3) read_frags(cur, kk + 1, a[f ^ 1], b[f ^ 1]);
-            else read_frags(nxt, 0, a[f ^ 1], b[f ^ 1]);
-            // decode groups 0,1 | 2 | 3 | - of the next step in slices 0 | 1 | 2 | 3
-            if (kk == 0) {
-                decode_group(nxt, 0, ca, cb);
-                decode_group(nxt, 1, ca, cb);
-            } else if (kk < 3) {
-                decode_group(nxt, kk + 1, ca, cb);
+        for (int q = 0; q < 16; ++q) {
+            const int slice = q >> 3, r = q & 7;
+            if (q == 13) __syncthreads();
+            // (on the final step the fragments come from a refilled stage nobody uses)
+            if (q < 13) read_a(cur, q + 3);
+            else read_a(nxt, q - 13);
+            if (q >= 2 && q < 6) read_b(cur, 1, q - 2);
+            else if (q == 13 || q == 14) {
+                read_b(nxt, 0, 2 * (q - 13));
+                read_b(nxt, 0, 2 * (q - 13) + 1);
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[f][j], a[f][i], acc[i][j], 0, 0, 0);
-            // issue order inside the slice: next fragments first, then each MFMA followed by a
-            // share of the decode, the decoded rows' LDS writes last
-            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-            if (kk == 0) {
-#pragma unroll
-                for (int m = 0; m < 8; ++m) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);
+            // the next step's eight decodes (A and B of each code group): one in each of groups 0-3,
+            // one in each two of groups 4-11
+            const int item = q < 4 ? q : 4 + ((q - 4) >> 1), g = item >> 1;
+            auto pieces = [&](auto qt) {
+                constexpr int Q = decltype(qt)::value;
+                if (q < 4) {
+                    if (item & 1) two_pieces<Q>(db, cb, g, tw);
+                    else two_pieces<Q>(da, ca, g, ta);
+                } else if (q < 12) {
+                    if (item & 1) {
+                        if (q & 1) db.template piece<Q + 4>(cb, g, tw);
+                        else db.template piece<Q>(cb, g, tw);
+                    } else {
+                        if (q & 1) da.template piece<Q + 4>(ca, g, ta);
+                        else da.template piece<Q>(ca, g, ta);
+                    }
                 }
-                __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
-            } else if (kk < 3) {
-#pragma unroll
-                for (int m = 0; m < 8; ++m) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
-                }
-                __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);
-            }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            // B fragments forth and back, so that neighbouring MFMAs share an operand
+            const int j0 = (r & 1) ? 3 : 0, dj = (r & 1) ? -1 : 1;
             __builtin_amdgcn_sched_barrier(0);
+            mfma16(acc[r][j0], b[slice][j0], a[q & 3]);
+            pieces(Piece<0>{});
+            mfma16(acc[r][j0 + dj], b[slice][j0 + dj], a[q & 3]);
+            pieces(Piece<1>{});
+            mfma16(acc[r][j0 + 2 * dj], b[slice][j0 + 2 * dj], a[q & 3]);
+            pieces(Piece<2>{});
+            mfma16(acc[r][j0 + 3 * dj], b[slice][j0 + 3 * dj], a[q & 3]);
+            pieces(Piece<3>{});
+            if (q < 4 || (q < 12 && (q & 1))) {
+                if (item & 1) *(uint4*)(lds + bdst[g] + nxt) = make_uint4(db.out[0], db.out[1], db.out[2], db.out[3]);
+                else *(uint4*)(lds + adst[g] + nxt) = make_uint4(da.out[0], da.out[1], da.out[2], da.out[3]);
+            }
         }
     };
 
+    // unrolled by four so that every register set and stage is a constant
     int s = 0;
-    for (; s + 2 < nk; s += 3) {
-        kstep(s, wa, wb, xa, xb);
-        kstep(s + 1, ya, yb, wa, wb);
-        kstep(s + 2, xa, xb, ya, yb);
+    for (; s + 3 < nk; s += 4) {
+        kstep(Piece<0>{}, s);
+        kstep(Piece<1>{}, s + 1);
+        kstep(Piece<2>{}, s + 2);
+        kstep(Piece<3>{}, s + 3);
     }
-    if (s < nk) kstep(s, wa, wb, xa, xb);
-    if (s + 1 < nk) kstep(s + 1, ya, yb, wa, wb);
+    if (s < nk) kstep(Piece<0>{}, s);
+    if (s + 1 < nk) kstep(Piece<1>{}, s + 1);
+    if (s + 2 < nk) kstep(Piece<2>{}, s + 2);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mfma_done(acc[i]);
 
     // epilogue.  The MFMAs computed the transposed tile, so element e of accumulator (i, j)
-    // belongs to row i*32 + lane%32 and column j*32 + 8*(e/4) + 4*(lane/32) + e%4: each lane
+    // belongs to row i*16 + lane%16 and column j*16 + 4*(lane/16) + e: each lane
     // holds runs of four consecutive columns of one row and stores them as one vector (16 bytes
     // of fp32 or 8 of bf16).
-    const int64_t col0 = n0 + wn * 64 + 4 * (lane >> 5);
-    uint2 rwv[2][4];  // bf16 r' of the lane's columns, four per (j, run)
+    const int64_t col0 = n0 + wn * 64 + 4 * (lane >> 4);
+    uint2 rwv[4], bv[4];  // bf16 r' and bias (zero without one) of the lane's columns, four per j
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int64_t c = col0 + j * 32 + 8 * q;
-            if (c + 3 < p.N && p.vec4) {
-                rwv[j][q] = *(const uint2*)(p.wn + c);
-            } else {
-                uint16_t v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = c + r < p.N ? p.wn[c + r] : (uint16_t)0;
-                rwv[j][q] = make_uint2(v[0] | ((uint32_t)v[1] << 16), v[2] | ((uint32_t)v[3] << 16));
-            }
-        }
+    for (int j = 0; j < 4; ++j) load_columns(p, col0 + j * 16, rwv[j], bv[j]);
     const bool plain = !p.bias && !p.gelu && !p.out_bf16;
-    // bf16 bias of the lane's columns, loaded once for its four rows (zero without a bias)
-    uint2 bv[2][4];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int64_t c = col0 + j * 32 + 8 * q;
-            if (p.bias && c + 3 < p.N && p.vec4) {
-                bv[j][q] = *(const uint2*)(p.bias + c);
-            } else {
-                uint16_t v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = p.bias && c + r < p.N ? p.bias[c + r] : (uint16_t)0;
-                bv[j][q] = make_uint2(v[0] | ((uint32_t)v[1] << 16), v[2] | ((uint32_t)v[3] << 16));
-            }
-        }
-    // the lane's four row norms before the first store (Y may alias xn as far as the compiler
+    // the lane's eight row norms before the first store (Y may alias xn as far as the compiler
     // knows, so a load after a store would wait for it)
-    float xsv[4];
+    float xsv[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t row = m0 + wm * 128 + i * 32 + (lane & 31);
+    for (int i = 0; i < 8; ++i) {
+        const int64_t row = m0 + wm * 128 + i * 16 + (lane & 15);
         xsv[i] = row < p.M ? p.xn[row] : 0.f;
     }
+    // the four outputs of accumulator (i, j)
+    auto outputs = [&](int i, int j) {
+        floatx4 v;
+        const float xs = xsv[i];
+        v[0] = acc[i][j][0] * xs * __uint_as_float(rwv[j].x << 16);
+        v[1] = acc[i][j][1] * xs * __uint_as_float(rwv[j].x & 0xFFFF0000u);
+        v[2] = acc[i][j][2] * xs * __uint_as_float(rwv[j].y << 16);
+        v[3] = acc[i][j][3] * xs * __uint_as_float(rwv[j].y & 0xFFFF0000u);
+        if (!plain) {
+            v[0] = epilogue_value(p, v[0], __uint_as_float(bv[j].x << 16));
+            v[1] = epilogue_value(p, v[1], __uint_as_float(bv[j].x & 0xFFFF0000u));
+            v[2] = epilogue_value(p, v[2], __uint_as_float(bv[j].y << 16));
+            v[3] = epilogue_value(p, v[3], __uint_as_float(bv[j].y & 0xFFFF0000u));
+        }
+        return v;
+    };
     // Rows that allow 4-wide stores (and a multiple of 4 columns): the finished outputs go through
     // LDS (free after the main loop) so that each store covers 4 rows of contiguous bytes (256 of
-    // fp32, 128 of bf16) instead of 32 rows of 16 or 8 bytes.  Each wave owns a region of 64 rows
+    // fp32, 128 of bf16) instead of 16 rows of 64 or 32 bytes.  Each wave owns a region of 64 rows
     // (68 floats or 72 bf16 per row, padding that keeps the accesses conflict-free) and turns its
     // 128 x 64 sub-tile around in two halves; a wave's LDS accesses run in order, so the halves
     // reuse the region without a barrier.
@@ -748,34 +915,19 @@ __global__ __launch_bounds__(512, 2) void lut_gemm_big(GemmParams p, int ntm, in
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii) {
-                const int i = 2 * half + ii;
-                const float xs = xsv[i];
-                const int lrow = ii * 32 + (lane & 31);
+            for (int ii = 0; ii < 4; ++ii) {
+                const int lrow = ii * 16 + (lane & 15);
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const uint2 rw = rwv[j][q];
-                        float v[4] = {acc[i][j][4 * q + 0] * xs * __uint_as_float(rw.x << 16),
-                                      acc[i][j][4 * q + 1] * xs * __uint_as_float(rw.x & 0xFFFF0000u),
-                                      acc[i][j][4 * q + 2] * xs * __uint_as_float(rw.y << 16),
-                                      acc[i][j][4 * q + 3] * xs * __uint_as_float(rw.y & 0xFFFF0000u)};
-                        const int lcol = j * 32 + 8 * q + 4 * (lane >> 5);
-                        if (!plain) {
-                            const uint2 b = bv[j][q];
-                            v[0] = epilogue_value(p, v[0], __uint_as_float(b.x << 16));
-                            v[1] = epilogue_value(p, v[1], __uint_as_float(b.x & 0xFFFF0000u));
-                            v[2] = epilogue_value(p, v[2], __uint_as_float(b.y << 16));
-                            v[3] = epilogue_value(p, v[3], __uint_as_float(b.y & 0xFFFF0000u));
-                        }
-                        if (p.out_bf16)
-                            *(uint2*)(tlb + lrow * TSB + lcol) =
-                                make_uint2(f32_to_bf16_rne(v[0]) | (f32_to_bf16_rne(v[1]) << 16),
-                                           f32_to_bf16_rne(v[2]) | (f32_to_bf16_rne(v[3]) << 16));
-                        else
-                            *(float4*)(tl + lrow * TS + lcol) = make_float4(v[0], v[1], v[2], v[3]);
-                    }
+                for (int j = 0; j < 4; ++j) {
+                    const floatx4 v = outputs(4 * half + ii, j);
+                    const int lcol = j * 16 + 4 * (lane >> 4);
+                    if (p.out_bf16)
+                        *(uint2*)(tlb + lrow * TSB + lcol) =
+                            make_uint2(f32_to_bf16_rne(v[0]) | (f32_to_bf16_rne(v[1]) << 16),
+                                       f32_to_bf16_rne(v[2]) | (f32_to_bf16_rne(v[3]) << 16));
+                    else
+                        *(floatx4*)(tl + lrow * TS + lcol) = v;
+                }
             }
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
@@ -793,52 +945,18 @@ __global__ __launch_bounds__(512, 2) void lut_gemm_big(GemmParams p, int ntm, in
         return;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t row = m0 + wm * 128 + i * 32 + (lane & 31);
+    for (int i = 0; i < 8; ++i) {
+        const int64_t row = m0 + wm * 128 + i * 16 + (lane & 15);
         if (row >= p.M) continue;
-        const float xs = xsv[i];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t c = col0 + j * 32 + 8 * q;
-                const uint2 rw = rwv[j][q];
-                float v[4] = {acc[i][j][4 * q + 0] * xs * __uint_as_float(rw.x << 16),
-                              acc[i][j][4 * q + 1] * xs * __uint_as_float(rw.x & 0xFFFF0000u),
-                              acc[i][j][4 * q + 2] * xs * __uint_as_float(rw.y << 16),
-                              acc[i][j][4 * q + 3] * xs * __uint_as_float(rw.y & 0xFFFF0000u)};
-                const bool full = c + 3 < p.N && p.vec4;
-                if (plain && full) {
-                    *(float4*)((float*)p.Y + row * p.ldy + c) = make_float4(v[0], v[1], v[2], v[3]);
-                    continue;
-                }
-                if (!plain) {
-                    const uint2 b = bv[j][q];
-                    v[0] = epilogue_value(p, v[0], __uint_as_float(b.x << 16));
-                    v[1] = epilogue_value(p, v[1], __uint_as_float(b.x & 0xFFFF0000u));
-                    v[2] = epilogue_value(p, v[2], __uint_as_float(b.y << 16));
-                    v[3] = epilogue_value(p, v[3], __uint_as_float(b.y & 0xFFFF0000u));
-                }
-                if (full && p.out_bf16) {
-                    *(uint2*)((uint16_t*)p.Y + row * p.ldy + c) =
-                        make_uint2(f32_to_bf16_rne(v[0]) | (f32_to_bf16_rne(v[1]) << 16),
-                                   f32_to_bf16_rne(v[2]) | (f32_to_bf16_rne(v[3]) << 16));
-                } else if (full) {
-                    *(float4*)((float*)p.Y + row * p.ldy + c) = make_float4(v[0], v[1], v[2], v[3]);
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (c + r < p.N) store_one(p, row, c + r, v[r]);
-                }
-            }
-        }
+        for (int j = 0; j < 4; ++j) store_four(p, row, col0 + j * 16, outputs(i, j));
     }
 }
 
 template <int BA, int BW>
 hipError_t launch_big(const GemmParams& p, hipStream_t stream) {
     static std::atomic<uint64_t> attr{0};
-    const size_t smem = (size_t)2 * 2 * LDS2_TILE * sizeof(__bf16) + (BA == 6 ? 64 * sizeof(uint32_t) : 0);
+    const size_t smem = (size_t)LDS2_BYTES + (BA == 6 ? 64 * sizeof(uint32_t) : 0);
     const hipError_t e = raise_lds_limit((const void*)lut_gemm_big<BA, BW>, (int)smem, attr);
     if (e != hipSuccess) return e;
     const int ntm = (int)((p.M + BM2 - 1) / BM2), ntn = (int)((p.N + BN2 - 1) / BN2);
@@ -934,7 +1052,7 @@ inline GemmParams rows_from(const GemmParams& p, int64_t m0, int ba) {
 
 template <int BA, int BW>
 hipError_t launch_one(const GemmParams& p, hipStream_t stream, int cus) {
-    const int64_t m_big = lut_gemm_big_rows(p.M, p.N, cus);
+    const int64_t m_big = lut_gemm_big_rows(p.M, p.N, p.K, cus);
     if (m_big == 0) return launch_small<BA, BW>(p, stream);
     if (m_big == p.M) return launch_big<BA, BW>(p, stream);
     GemmParams head = p;
@@ -946,11 +1064,12 @@ hipError_t launch_one(const GemmParams& p, hipStream_t stream, int cus) {
 
 }  // namespace
 
-int64_t lut_gemm_big_rows(int64_t M, int64_t N, int cus) {
+int64_t lut_gemm_big_rows(int64_t M, int64_t N, int64_t K, int cus) {
     // the large kernel from one 256x256 tile per compute unit up (measured: at 432 tiles on 256
     // compute units it beats the 128x128 kernel by a quarter, despite its half-empty second round)
     const int64_t ntm = (M + BM2 - 1) / BM2, ntn = (N + BN2 - 1) / BN2, tiles = ntm * ntn;
-    if (tiles < (int64_t)cus) return 0;
+    // (its 32-bit code offsets cover rows up to MAX_K2 inputs)
+    if (tiles < (int64_t)cus || K > MAX_K2) return 0;
     // Wave quantization: the large kernel runs one tile per compute unit at a time, so a last round
     // that is only partly full costs as long as a full one (c4's down-projection: 2600 tiles, an
     // eleventh round of 40).  When that pays, the large kernel takes the tile rows that fill its
