@@ -278,7 +278,8 @@ orbit_status orbit_qlinear_workspace_size(int64_t M, int64_t N, int64_t K, size_
  * 128 x 128-tile kernel, the latter split over K into `splits` contiguous ranges (1 = unsplit)
  * when orbit_qlinear_ws has a workspace of orbit_qlinear_workspace_size(M, N, K) bytes.  For
  * profiling and for callers that time or place the two parts themselves; the layer calls make the
- * same choice internally.
+ * same choice internally, except that the rows of a small grid run on a third kernel where it is
+ * the faster one, which splits the contraction inside each workgroup and needs no workspace.
  *   rows_large, splits  host, out
  * Errors: ORBIT_EINVAL (null outputs, negative M or N, K not a positive multiple of 64 up to
  * 2^30); ORBIT_EHIP (no device).  M = 0 or N = 0 gives 0 and 1.
@@ -290,7 +291,8 @@ orbit_status orbit_qlinear_schedule(int64_t M, int64_t N, int64_t K, int64_t* ro
  * workspace_bytes at least orbit_qlinear_workspace_size(M, N, K) on the same device (and the
  * workspace 16-byte aligned) the rows of a small grid run split over K: the splits' fp32 sums
  * are added in split order (deterministic for a given device) before the epilogue, so the result
- * differs from orbit_qlinear_ex's only in the fp32 rounding of the sum over K.  Otherwise (a
+ * differs from orbit_qlinear_ex's only in the fp32 rounding of the sum over K (rows that run
+ * faster without their partial sums leaving the workgroup do so).  Otherwise (a
  * NULL or too small workspace, or a layer that does not split) it is orbit_qlinear_ex.  The
  * workspace's contents on entry do not matter.  The library does not keep the pointer; the
  * caller keeps the workspace alive and unused by other work until the call's work on `stream`
