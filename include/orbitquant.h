@@ -278,8 +278,9 @@ orbit_status orbit_qlinear_workspace_size(int64_t M, int64_t N, int64_t K, size_
  * 128 x 128-tile kernel, the latter split over K into `splits` contiguous ranges (1 = unsplit)
  * when orbit_qlinear_ws has a workspace of orbit_qlinear_workspace_size(M, N, K) bytes.  For
  * profiling and for callers that time or place the two parts themselves; the layer calls make the
- * same choice internally, except that the rows of a small grid run on a third kernel where it is
- * the faster one, which splits the contraction inside each workgroup and needs no workspace.
+ * same choice internally, except that the rows of a small grid run on the 256 x 256-tile kernel, or
+ * on a third one that splits the contraction inside each workgroup, where those are faster; neither
+ * needs the workspace.
  *   rows_large, splits  host, out
  * Errors: ORBIT_EINVAL (null outputs, negative M or N, K not a positive multiple of 64 up to
  * 2^30); ORBIT_EHIP (no device).  M = 0 or N = 0 gives 0 and 1.

@@ -128,8 +128,6 @@ struct WaveTile {
     int mt, nt, waves;
 };
 WaveTile lut_gemm_wave_tile(int64_t M, int64_t N, int64_t K, int cus);
-// Whether that is the faster kernel for rows the 128x128 kernel would run split `splits` ways
-bool lut_gemm_wave_wins(int64_t M, int64_t N, int64_t K, int ba, int bw, int splits, int split_steps, int cus);
 hipError_t launch_lut_gemm_wave(const GemmParams& p, int ba, int bw, int cus, hipStream_t stream);
 
 // INT4 round-to-nearest (group 64) weight-only layer of the AdaLN modulation projections.

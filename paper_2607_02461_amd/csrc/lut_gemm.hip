@@ -730,10 +730,53 @@ __global__ __launch_bounds__(256) void lut_gemm_reduce(GemmParams p, int splits)
     }
 }
 
+// The kernel for rows that do not fill the device with large tiles.  Estimated microseconds of each,
+// within 15% of 60 measured shapes (M 1 .. 20000, N 768 .. 15360, K 1024 .. 16384, four bit pairs, on
+// 256 compute units); a tie stays on the 128 x 128 kernel.
+enum class Kernel { kSmall, kWave, kLarge };
+
+Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int splits, int split_steps, int cus) {
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    // decode cost relative to 4-bit codes, per operand: 1.3 at 3 bits, 1.85 at 6
+    auto cost = [](int b) { return b == 3 ? 1.3 : b == 6 ? 1.85 : 1.0; };
+    const double f = 0.5 * (cost(ba) + cost(bw)), steps = (double)(K / BK);
+    // 128 x 128: k co-resident workgroups per compute unit take 0.58, 1.03, 1.64 and 2.13 us per K-step
+    // for k = 1 .. 4, 0.48 us each beyond; splitting adds the partial sums' round trip and the reduction
+    const int64_t wgs = tiles(BM, BN) * splits, k = (wgs + cus - 1) / cus;
+    const double step = k == 1 ? 0.58 : k == 2 ? 1.03 : k == 3 ? 1.64 : k == 4 ? 2.13 : 0.48 * (double)wgs / cus;
+    double best = 0.95 * (7.5 + step * (0.25 + 0.75 * f) * (splits > 1 ? (double)split_steps : steps) +
+                          (splits > 1 ? 2.0 + (double)splits * (double)M * (double)N * 8.0 / 4.2e6 : 0.0));
+    Kernel kernel = Kernel::kSmall;
+    // 256 x 256, one round: 1.27 us per K-step while up to 0.6 of the compute units have a tile, 1.52 us
+    // when all do (the clock falls).  4429 x 3072 x 3072 W3A3: 85 us against 129 on 128 x 128 tiles;
+    // 4608 x 3072 x 12288 W4A4 280 against 408, 2048 x 5120 x 5120 113 against 138 (135 on wave tiles).
+    const int64_t large = tiles(BM2, BN2);
+    if (large <= cus && K <= MAX_K2) {
+        const double full = std::max(0.0, (double)large / cus - 0.6) / 0.4;
+        const double t = 10.0 + steps * (1.27 + 0.25 * full) * (0.5 + 0.5 * f);
+        if (t < best) {
+            best = t;
+            kernel = Kernel::kLarge;
+        }
+    }
+    // wave tiles, whole chunks of 128 only: the busiest compute unit's tiles, 0.346 us per
+    // 64 x 64 x 128 chunk, others in proportion to their decode
+    if (K % 128 == 0 && (M + 15) / 16 <= 65535) {
+        const WaveTile w = lut_gemm_wave_tile(M, N, K, cus);
+        const int64_t per_cu = (tiles(16 * w.mt, 16 * w.nt) + cus - 1) / cus;
+        const double t = 4.5 + (double)per_cu * (double)(K / 128) * 0.346 * f * (w.mt + w.nt) / 8.0;
+        if (t < best) kernel = Kernel::kWave;
+    }
+    return kernel;
+}
+
 template <int BA, int BW>
 hipError_t launch_small(const GemmParams& p, hipStream_t stream, int cus) {
-    if (lut_gemm_wave_wins(p.M, p.N, p.K, BA, BW, p.ws ? p.splits : 1, p.split_steps, cus))
-        return launch_lut_gemm_wave(p, BA, BW, cus, stream);
+    switch (fastest_kernel(p.M, p.N, p.K, BA, BW, p.ws ? p.splits : 1, p.split_steps, cus)) {
+        case Kernel::kWave: return launch_lut_gemm_wave(p, BA, BW, cus, stream);
+        case Kernel::kLarge: return launch_big<BA, BW>(p, stream);
+        default: break;
+    }
     dim3 grid((unsigned)((p.N + BN - 1) / BN), (unsigned)((p.M + BM - 1) / BM));
     const size_t smem = (size_t)2 * 2 * SMALL_TILE * sizeof(__bf16) + (BA == 6 ? 64 * sizeof(uint32_t) : 0);
     static std::atomic<uint64_t> attr_split{0}, attr_whole{0};

@@ -175,26 +175,6 @@ WaveTile lut_gemm_wave_tile(int64_t M, int64_t N, int64_t K, int cus) {
     return t;
 }
 
-bool lut_gemm_wave_wins(int64_t M, int64_t N, int64_t K, int ba, int bw, int splits, int split_steps, int cus) {
-    // whole chunks only, and a launch grid's second dimension
-    if (K % KC != 0 || (M + 15) / 16 > 65535) return false;
-    // Estimated microseconds on both kernels, within 15% of 60 measured shapes; a tie stays on the
-    // 128 x 128 kernel.  Decode cost relative to 4-bit codes, per operand: 1.3 at 3 bits, 1.85 at 6.
-    auto cost = [](int b) { return b == 3 ? 1.3 : b == 6 ? 1.85 : 1.0; };
-    const double f = 0.5 * (cost(ba) + cost(bw));
-    // here: the busiest compute unit's tiles, 0.346 us per 64 x 64 x 128 chunk, in proportion to its decode
-    const WaveTile t = lut_gemm_wave_tile(M, N, K, cus);
-    const int64_t tiles = ((M + 16 * t.mt - 1) / (16 * t.mt)) * ((N + 16 * t.nt - 1) / (16 * t.nt));
-    const double here = 4.5 + (double)((tiles + cus - 1) / cus) * (double)(K / KC) * 0.346 * f * (t.mt + t.nt) / 8.0;
-    // there: k co-resident workgroups per compute unit take 0.58, 1.03, 1.64 and 2.13 us per K-step of 64
-    // for k = 1 .. 4, 0.48 us each beyond; splitting adds the partial sums' round trip and the reduction
-    const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * splits, k = (wgs + cus - 1) / cus;
-    const double step = k == 1 ? 0.58 : k == 2 ? 1.03 : k == 3 ? 1.64 : k == 4 ? 2.13 : 0.48 * (double)wgs / cus;
-    const double there = 7.5 + step * (0.25 + 0.75 * f) * (splits > 1 ? split_steps : (int)(K / 64)) +
-                         (splits > 1 ? 2.0 + (double)splits * (double)M * (double)N * 8.0 / 4.2e6 : 0.0);
-    return here < 0.95 * there;
-}
-
 hipError_t launch_lut_gemm_wave(const GemmParams& p, int ba, int bw, int cus, hipStream_t stream) {
     const WaveTile t = lut_gemm_wave_tile(p.M, p.N, p.K, cus);
     switch (ba * 8 + bw) {

@@ -76,6 +76,18 @@ def test_random_codes_large_tiles(M, N, K, ba, bw):
     assert worst_row <= GEMM_REL_F
 
 
+# rows that do not fill the device with large tiles run on them all the same where that is the fastest
+# kernel (from about 130 tiles on 256 compute units): ragged grids of 144 and 221 tiles, step counts that
+# leave every remainder of the large kernel's ring of four code sets
+@pytest.mark.parametrize("M,N,K", [(3000, 3001, 3072), (3300, 4100, 1344), (3300, 4100, 1408), (3300, 4100, 1472)])
+@pytest.mark.parametrize("ba,bw", [(4, 4), (3, 3), (6, 3)])
+def test_random_codes_partial_round_of_large_tiles(M, N, K, ba, bw):
+    xc, xs, wc, wr = _inputs(M, N, K, ba, bw, seed=M + N + K)
+    Y = _gpu(xc, xs, wc, wr, ba, bw, K)
+    args = (xc.numpy(), xs.double().numpy(), ba, wc.numpy(), wr.double().numpy(), bw, K)
+    check_gemm(f"gemm partial round M={M} N={N} K={K} W{bw}A{ba}", Y, qlinear_oracle_bf16(*args), _scale(*args), K)
+
+
 # the fused layer epilogue (bias, GELU, bf16 output) on both kernels, with vector and element-wise
 # stores (ldy a multiple of 4 or not); with N and ldy multiples of 4 the outputs go through the
 # kernels' LDS turn-around
