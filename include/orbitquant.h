@@ -362,7 +362,7 @@ orbit_status adaln_int4_quantize_weights(const uint16_t* W, int64_t N, int64_t K
  *
  *   X       device, bf16 [M][ldx]; ldx >= K and a multiple of 8; K <= 16384 (the tokens are
  *           staged in LDS)
- *   M       tokens; 0 <= M <= 131070 (rows are processed two at a time per weight pass)
+ *   M       tokens; 0 <= M <= 131070 (up to four at a time per pass over the weights)
  *   q, scales, N, K   as produced by adaln_int4_quantize_weights
  *   bias    device, bf16 [N], or NULL
  *   Y       device, fp32 [M][ldy], ldy >= N

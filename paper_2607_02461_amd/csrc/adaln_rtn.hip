@@ -12,9 +12,7 @@
 //
 // Online: Y = X (q * scale)^T (+ bias) for a handful of BF16 rows of X.  The layer streams its
 // weights once, so it is bound by HBM and, a few microseconds long per projection, by how much
-// of it is in flight: groups of 16 lanes own two output rows, each lane issues the loads of up
-// to four 32-code chunks per row before computing, and the activations sit in LDS, staged once
-// by each persistent workgroup.  A code nibble u becomes the BF16 value 128 + u by OR-ing it into
+// of it is in flight.  A code nibble u becomes the BF16 value 128 + u by OR-ing it into
 // the mantissa of 128 (0x4300 | u is exact: 128..143 are BF16 integers), two per register at
 // bits 0 and 16, so one v_dot2_f32_bf16 takes two codes against two activations with exact
 // products; per chunk the accumulator starts at -136 * sum(x), which removes the 128 + 8 offset.
@@ -31,6 +29,7 @@ namespace orbit {
 namespace {
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRtnGroup = 64;
 
@@ -90,128 +89,188 @@ __device__ __forceinline__ float dpp_add(float v) {
     return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
-// Rows of Y per 16-lane group, groups per workgroup (a block of 32 rows), and chunks (32 codes)
-// whose loads a lane issues before it computes any of them.
-constexpr int kRtnRows = 2;
+// A workgroup of 256 threads is 16 groups of 16 lanes, a row of Y each; a lane takes every sixteenth
+// chunk (32 codes) of its row and has the loads of up to kRtnBatch of them in flight, all of a row up to
+// K = 3072.  One projection is 29 MB and a few microseconds, so what counts is the chain of latencies in
+// front of the last byte: the weights' loads are issued right behind the tokens' and before anything
+// waits for those, the chunk sums come out of the staging registers (no second barrier), and one row
+// per group spreads 18432 rows over 4.5 workgroups per compute unit instead of 2.25.  Measured, device
+// time: 1 x 3072 -> 18432 11.5 -> 9.6 us (3.2 TB/s; an empty launch is 2.8 us of it), 9216 rows 8.7 -> 7.3,
+// 1 x 5120 -> 60001 37 -> 34, 4 x 5120 -> 40000 54 -> 45 (one pass over the weights instead of two),
+// 1 x 3072 -> 1050624 316 -> 318 (5.4 TB/s).
 constexpr int kRtnLanes = 16;
-constexpr int kRtnGroupsPerWg = 16;
-constexpr int kRtnBatch = 4;
-constexpr int kRtnBlockRows = kRtnRows * kRtnGroupsPerWg;
+constexpr int kRtnBlockRows = 16;
+constexpr int kRtnBatch = 6;
 
 // Persistent: a workgroup stages its tokens once, then walks row blocks blockIdx.x, +gridDim.x, ...
-template <int MT>
+template <int MT, bool STREAM>
 __global__ __launch_bounds__(256) void adaln_int4_linear_kernel(RtnLinearParams p) {
-    // activations of the workgroup's MT tokens, paired per 8 as (x0,x4) (x1,x5) (x2,x6) (x3,x7),
-    // then one fp32 sum per chunk of 32
-    extern __shared__ __align__(16) uint32_t xlds[];
-    const int nchunk = p.K / 32;
-    float* const csum = (float*)(xlds + MT * (p.K / 2));
+    // The workgroup's MT tokens, paired per 8 as (x0,x4) (x1,x5) (x2,x6) (x3,x7): 16-byte vector t of
+    // chunk c sits at t * nchunk + c, so that 16 lanes reading 16 chunks read 256 contiguous bytes
+    // (chunk by chunk their vectors would be 64 bytes apart, four to a bank).  Then one fp32 sum per chunk.
+    extern __shared__ __align__(16) uint4 xlds[];
+    const int nchunk = p.K / 32, nvec = p.K / 8;
+    float* const csum = (float*)(xlds + MT * nvec);
     const int m0 = blockIdx.y * MT;
     const uint32_t magic = 0x43004300u, one_one = 0x3F803F80u;
 
-    for (int i = threadIdx.x; i < MT * (p.K / 8); i += blockDim.x) {
-        const int m = i / (p.K / 8), t = i - m * (p.K / 8);
-        const uint4 v = *(const uint4*)(p.X + (int64_t)min(m0 + m, (int)p.M - 1) * p.ldx + (int64_t)t * 8);
-        *(uint4*)(xlds + m * (p.K / 2) + t * 4) =
+    auto token_load = [&](int i) {
+        const int m = i / nvec, v = i - m * nvec;
+        return *(const uint4*)(p.X + (int64_t)min(m0 + m, (int)p.M - 1) * p.ldx + (int64_t)v * 8);
+    };
+    // i runs over whole quads of lanes (nvec is a multiple of 8), one chunk each
+    auto token_store = [&](int i, const uint4& v) {
+        const int m = i / nvec, j = i - m * nvec;
+        float sum = dot2(v.w, one_one, dot2(v.z, one_one, dot2(v.y, one_one, dot2(v.x, one_one, 0.f))));
+        sum = dpp_add<0xB1>(sum);  // quad_perm [1,0,3,2]
+        sum = dpp_add<0x4E>(sum);  // quad_perm [2,3,0,1]
+        xlds[m * nvec + (j & 3) * nchunk + (j >> 2)] =
             make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
                        __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < MT * nchunk; i += blockDim.x) {
-        const uint32_t* w = xlds + (i / nchunk) * (p.K / 2) + (i % nchunk) * 16;
-        float sum = 0.f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) sum = dot2(w[k], one_one, sum);
-        csum[i] = sum;
-    }
-    __syncthreads();
+        if ((j & 3) == 0) csum[m * nchunk + (j >> 2)] = sum;
+    };
 
     const int lane = threadIdx.x & (kRtnLanes - 1), grp = threadIdx.x / kRtnLanes;
-    const int64_t qrow = p.K / 2, srow = p.K / kRtnGroup;
+    const uint32_t qrow = p.K / 2, srow = p.K / kRtnGroup * 2;  // bytes
+    const uint32_t qoff = grp * qrow + lane * 16, soff = grp * srow + (lane >> 1) * 2;
     const int64_t nblocks = (p.N + kRtnBlockRows - 1) / kRtnBlockRows;
-    for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
-        const int64_t n0 = blk * kRtnBlockRows + grp * kRtnRows;
-        int64_t nrow[kRtnRows];
-#pragma unroll
-        for (int r = 0; r < kRtnRows; ++r) nrow[r] = min(n0 + r, p.N - 1);  // the ragged end re-reads the last row
-        float tot[kRtnRows][MT];
-#pragma unroll
-        for (int r = 0; r < kRtnRows; ++r)
-#pragma unroll
-            for (int m = 0; m < MT; ++m) tot[r][m] = 0.f;
+    u32x4 cw[kRtnBatch];
+    uint16_t sc[kRtnBatch];
+    // A batch's loads, through its block's rows as a buffer: rows past the last one read zero, chunks
+    // past a row's end the next row's (dropped below), and no address is formed per load.
+    struct Batch {
+        __amdgpu_buffer_rsrc_t q, s;
+        int c0, slots;  // first chunk, slots of 16 chunks (uniform; 0: there is no such batch)
+    };
+    auto batch_at = [&](int64_t blk, int c0) {
+        Batch t;
+        const int64_t n0 = min(blk, nblocks - 1) * kRtnBlockRows;
+        const int rows = (int)min((int64_t)kRtnBlockRows, p.N - n0);
+        t.q = __builtin_amdgcn_make_buffer_rsrc((void*)(p.q + n0 * qrow), 0, rows * (int)qrow, 0x00027000);
+        t.s = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)p.scales + n0 * srow), 0, rows * (int)srow, 0x00027000);
+        t.c0 = c0;
+        t.slots = blk < nblocks ? min(kRtnBatch, (nchunk - c0 + kRtnLanes - 1) / kRtnLanes) : 0;
+        return t;
+    };
+    auto weight_load = [&](const Batch& t, int b) {
+        if (b < t.slots) {
+            cw[b] = __builtin_amdgcn_raw_buffer_load_b128(t.q, qoff + 256 * b, t.c0 * 16, 0);
+            sc[b] = __builtin_amdgcn_raw_buffer_load_b16(t.s, soff + 16 * b, t.c0, 0);
+        }
+    };
 
-        for (int c0 = 0; c0 < nchunk; c0 += kRtnLanes * kRtnBatch) {
-            // every load of the batch first; chunks past the end re-read the last one with scale 0
-            uint4 cw[kRtnBatch][kRtnRows];
-            float sc[kRtnBatch][kRtnRows];
-            int cidx[kRtnBatch];
+    const int total = MT * nvec, i1 = threadIdx.x + 256;
+    uint4 v0 = make_uint4(0u, 0u, 0u, 0u), v1 = v0;
+    if ((int)threadIdx.x < total) v0 = token_load(threadIdx.x);
+    if (i1 < total) v1 = token_load(i1);
+    Batch cur = batch_at(blockIdx.x, 0);
 #pragma unroll
-            for (int b = 0; b < kRtnBatch; ++b) {
-                const int c = c0 + lane + kRtnLanes * b;
-                cidx[b] = min(c, nchunk - 1);
-                if (c0 + kRtnLanes * b >= nchunk) continue;  // the whole slot is past the end (uniform)
+    for (int b = 0; b < kRtnBatch; ++b) weight_load(cur, b);
+    if ((int)threadIdx.x < total) token_store(threadIdx.x, v0);
+    if (i1 < total) token_store(i1, v1);
+    for (int i = threadIdx.x + 512; i < total; i += 256) token_store(i, token_load(i));
+    __syncthreads();
+
+    auto contract = [&](int b, int c0, float (&tot)[MT]) {
+        const int c = c0 + lane + kRtnLanes * b, cc = min(c, nchunk - 1);
+        float acc[MT];
 #pragma unroll
-                for (int r = 0; r < kRtnRows; ++r) {
-                    cw[b][r] = *(const uint4*)(p.q + nrow[r] * qrow + (int64_t)cidx[b] * 16);
-                    const float sv = (float)__builtin_bit_cast(_Float16, p.scales[nrow[r] * srow + (cidx[b] >> 1)]);
-                    sc[b][r] = c < nchunk ? sv : 0.f;
-                }
+        for (int m = 0; m < MT; ++m) acc[m] = -136.f * csum[m * nchunk + cc];
+        const uint32_t words[4] = {cw[b].x, cw[b].y, cw[b].z, cw[b].w};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint32_t u[4];  // (128 + u_j, 128 + u_{j+4}) of 8 codes, as BF16 pairs
+#pragma unroll
+            for (int j = 0; j < 4; ++j) u[j] = ((words[t] >> (4 * j)) & 0x000F000Fu) | magic;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const uint4 x = xlds[m * nvec + t * nchunk + cc];
+                acc[m] = dot2(u[0], x.x, acc[m]);
+                acc[m] = dot2(u[1], x.y, acc[m]);
+                acc[m] = dot2(u[2], x.z, acc[m]);
+                acc[m] = dot2(u[3], x.w, acc[m]);
             }
+        }
+        const float s = (float)__builtin_bit_cast(_Float16, sc[b]);
 #pragma unroll
-            for (int b = 0; b < kRtnBatch; ++b) {
-                if (c0 + kRtnLanes * b >= nchunk) break;  // uniform: no chunk of this slot exists
-                uint32_t xp[MT][16];
-                float xs[MT];
+        for (int m = 0; m < MT; ++m) tot[m] = c < nchunk ? fmaf(s, acc[m], tot[m]) : tot[m];
+    };
+    for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
+        float tot[MT];
 #pragma unroll
-                for (int m = 0; m < MT; ++m) {
-                    const uint4* src = (const uint4*)(xlds + m * (p.K / 2) + cidx[b] * 16);
+        for (int m = 0; m < MT; ++m) tot[m] = 0.f;
+        for (int c0 = 0; c0 < nchunk; c0 += kRtnLanes * kRtnBatch) {
+            if constexpr (STREAM) {
+                // the next batch, of this row or of the next block's: its loads take each slot's registers
+                // as soon as they are free, so that as much is in flight in every round as in the first
+                const Batch next = c0 + kRtnLanes * kRtnBatch < nchunk ? batch_at(blk, c0 + kRtnLanes * kRtnBatch)
+                                                                       : batch_at(blk + gridDim.x, 0);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const uint4 v = src[k];
-                        xp[m][4 * k] = v.x;
-                        xp[m][4 * k + 1] = v.y;
-                        xp[m][4 * k + 2] = v.z;
-                        xp[m][4 * k + 3] = v.w;
-                    }
-                    xs[m] = csum[m * nchunk + cidx[b]];
+                for (int b = 0; b < kRtnBatch; ++b) {
+                    if (b < cur.slots) contract(b, c0, tot);  // (uniform)
+                    weight_load(next, b);
+                    __builtin_amdgcn_sched_barrier(0);  // one chunk's token reads at a time (registers)
+                }
+                cur = next;
+            } else {
+                if (c0 > 0 || blk != blockIdx.x) {
+                    cur = batch_at(blk, c0);
+#pragma unroll
+                    for (int b = 0; b < kRtnBatch; ++b) weight_load(cur, b);
                 }
 #pragma unroll
-                for (int r = 0; r < kRtnRows; ++r) {
-                    const uint32_t words[4] = {cw[b][r].x, cw[b][r].y, cw[b][r].z, cw[b][r].w};
-                    uint32_t u[16];  // (128 + u_j, 128 + u_{j+4}) of each 8 codes, as BF16 pairs
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-#pragma unroll
-                        for (int jj = 0; jj < 4; ++jj) u[4 * t + jj] = ((words[t] >> (4 * jj)) & 0x000F000Fu) | magic;
-#pragma unroll
-                    for (int m = 0; m < MT; ++m) {
-                        float acc = -136.f * xs[m];
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) acc = dot2(u[k], xp[m][k], acc);
-                        tot[r][m] = fmaf(sc[b][r], acc, tot[r][m]);
-                    }
+                for (int b = 0; b < kRtnBatch; ++b) {
+                    if (c0 + kRtnLanes * b >= nchunk) break;  // uniform: no chunk of this slot exists
+                    contract(b, c0, tot);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
 
         // fixed-order sum over the 16 lanes of the group (one DPP row): pairs, quads, 8, 16
+        const int64_t n = blk * kRtnBlockRows + grp;
 #pragma unroll
-        for (int r = 0; r < kRtnRows; ++r) {
-#pragma unroll
-            for (int m = 0; m < MT; ++m) {
-                float v = tot[r][m];
-                v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
-                v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
-                v = dpp_add<0x141>(v);  // row_half_mirror
-                v = dpp_add<0x140>(v);  // row_mirror
-                const int64_t n = n0 + r;
-                if (lane == 0 && n < p.N && m0 + m < p.M) {
-                    if (p.bias) v += __uint_as_float((uint32_t)p.bias[n] << 16);
-                    p.Y[(int64_t)(m0 + m) * p.ldy + n] = v;
-                }
+        for (int m = 0; m < MT; ++m) {
+            float v = tot[m];
+            v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
+            v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
+            v = dpp_add<0x141>(v);  // row_half_mirror
+            v = dpp_add<0x140>(v);  // row_mirror
+            if (lane == 0 && n < p.N && m0 + m < p.M) {
+                if (p.bias) v += __uint_as_float((uint32_t)p.bias[n] << 16);
+                p.Y[(int64_t)(m0 + m) * p.ldy + n] = v;
             }
         }
     }
+}
+
+template <int MT, bool STREAM>
+hipError_t launch_grid(const RtnLinearParams& p, unsigned gx, hipStream_t stream) {
+    const size_t lds = (size_t)MT * (p.K / 8) * sizeof(uint4) + (size_t)MT * (p.K / 32) * sizeof(float);
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> attr{0};
+        const hipError_t e = raise_lds_limit((const void*)adaln_int4_linear_kernel<MT, STREAM>, 160 * 1024, attr);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((adaln_int4_linear_kernel<MT, STREAM>), dim3(gx, (unsigned)((p.M + MT - 1) / MT)), dim3(256), lds,
+                       stream, p);
+    return hipGetLastError();
+}
+
+template <int MT>
+hipError_t launch_linear(const RtnLinearParams& p, int cus, hipStream_t stream) {
+    // Workgroups walk the row blocks, the same number of blocks each as far as that goes: six per compute
+    // unit, where their waves cover each other's latencies.  One token against hundreds of thousands of
+    // rows (a step's projections in one call) is a long stream instead: eight leaner ones with the next
+    // rows' loads always in flight (1050624 x 3072: 318 against 350 us; 60001 x 5120: 37 against 33).
+    const int64_t nblocks = (p.N + kRtnBlockRows - 1) / kRtnBlockRows;
+    const bool stream_rows = MT == 1 && nblocks > (int64_t)48 * cus;
+    // (two tokens take 160 registers: three workgroups are what a compute unit holds)
+    const int64_t most = (int64_t)(stream_rows ? 8 : MT == 2 && nblocks > (int64_t)6 * cus ? 3 : 6) * cus, rounds = (nblocks + most - 1) / most;
+    const unsigned gx = (unsigned)((nblocks + rounds - 1) / rounds);
+    if constexpr (MT == 1)
+        if (stream_rows) return launch_grid<1, true>(p, gx, stream);
+    return launch_grid<MT, false>(p, gx, stream);
 }
 
 }  // namespace
@@ -226,20 +285,10 @@ hipError_t launch_adaln_int4_quantize(const uint16_t* W, int64_t N, int K, int64
 }
 
 hipError_t launch_adaln_int4_linear(const RtnLinearParams& p, int cus, hipStream_t stream) {
-    // up to four resident workgroups per compute unit walk the row blocks
-    const int64_t nblocks = (p.N + kRtnBlockRows - 1) / kRtnBlockRows;
-    const unsigned gx = (unsigned)std::min<int64_t>(nblocks, (int64_t)4 * cus);
-    const int mt = p.M == 1 ? 1 : 2;
-    const size_t lds = (size_t)mt * (p.K / 2) * sizeof(uint32_t) + (size_t)mt * (p.K / 32) * sizeof(float);
-    if (mt == 1) {
-        hipLaunchKernelGGL(adaln_int4_linear_kernel<1>, dim3(gx, 1), dim3(256), lds, stream, p);
-    } else {
-        static std::atomic<uint64_t> attr{0};
-        const hipError_t e = raise_lds_limit((const void*)adaln_int4_linear_kernel<2>, 80 * 1024, attr);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(adaln_int4_linear_kernel<2>, dim3(gx, (unsigned)((p.M + 1) / 2)), dim3(256), lds, stream, p);
-    }
-    return hipGetLastError();
+    // one pass over the weights per four tokens, or two where four would leave half a pass empty
+    if (p.M == 1) return launch_linear<1>(p, cus, stream);
+    if (p.M % 4 == 1 || p.M % 4 == 2) return launch_linear<2>(p, cus, stream);
+    return launch_linear<4>(p, cus, stream);
 }
 
 }  // namespace orbit

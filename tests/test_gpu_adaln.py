@@ -87,6 +87,25 @@ def test_linear_strided_input_and_padded_output():
     assert not torch.isnan(out).any()
 
 
+# long streams: one token against more than 48 row blocks of 16 per compute unit (196608 rows on 256), with
+# the next rows' loads in flight across blocks; whole and ragged blocks, one and two batches of chunks, a
+# partial slot of chunks; the same rows in two short calls give the same bits
+@pytest.mark.parametrize("M,N,K", [(1, 200000, 128), (1, 197007, 3136), (2, 100001, 192), (4, 50001, 1600)])
+def test_long_streams(M, N, K):
+    W = _weights(N, K, seed=N)
+    q, s = oq.adaln_int4_quantize_weights(W)
+    X = workloads.adaln_tokens(M, K, seed=K, device=DEV)
+    Y = oq.adaln_int4_linear(X, q, s)
+    h = N // 3 // 16 * 16
+    parts = [oq.adaln_int4_linear(X, q[:h], s[:h]), oq.adaln_int4_linear(X, q[h:], s[h:])]
+    torch.cuda.synchronize()
+    assert torch.equal(Y, torch.cat(parts, dim=1))
+    rows = torch.tensor([0, 1, 15, 16, 4095, N // 2, N - 2, N - 1], device=DEV)
+    oqq, osc = oracle.rtn_int4_quantize(to_f64(W[rows]))
+    ref = oracle.rtn_int4_linear(to_f64(X), oqq, osc)
+    assert rel_frobenius(Y[:, rows].double().cpu().numpy(), ref) <= GEMM_REL_F
+
+
 @pytest.mark.parametrize("N", [18432, 9216])
 def test_flux_shaped_projection(N):
     # the benchmark's layer shapes: one conditioning token, 3072 -> 6 x 3072 and 3 x 3072
