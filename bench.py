@@ -66,7 +66,7 @@ def source_digest():
     """Digest of the kernel sources; traffic counters taken from other sources are not used."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("rpbh_quantize.hip", "rpbh_quantize_row.hip", "lut_gemm.hip"):
+    for f in ("rpbh_quantize.hip", "rpbh_quantize_row.hip", "lut_gemm.hip", "lut_decode.h"):
         with open(os.path.join(ROOT, "paper_2607_02461_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
