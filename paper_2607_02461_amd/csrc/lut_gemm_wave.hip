@@ -6,7 +6,7 @@
 // memory and a second launch.  Here every wave contracts its own chunks of K, decodes both operands
 // straight into MFMA fragments (no LDS and no barrier in the loop, so waves never wait for each
 // other) and the partial sums meet once, in LDS, in wave order (deterministic).  The price is that
-// the decode is not shared: 28 (mt + nt) VALU operations of decode per 32 inputs behind mt nt MFMAs, and
+// the decode is not shared: 14 (mt + nt) VALU operations of decode (4-bit codes) go with mt nt MFMAs, and
 // the VALU bounds it (4 x 4 tiles: 700-800 TFLOP/s once the device is full, against 1340 for
 // the large kernel).  Loads are 16-byte vectors of 32 codes (at 4 bits), one or two chunks ahead.
 //
@@ -160,12 +160,12 @@ hipError_t launch_wave(const GemmParams& p, const WaveTile& t, hipStream_t strea
 
 WaveTile lut_gemm_wave_tile(int64_t M, int64_t N, int64_t K, int cus) {
     auto tiles = [&](int mt, int nt) { return ((M + 16 * mt - 1) / (16 * mt)) * ((N + 16 * nt - 1) / (16 * nt)); };
-    // The largest tile that still gives 0.7 workgroups per compute unit (decode per flop falls with
-    // the tile, but 48 tiles of 64 x 64 take 1.4 times as long as 192 of 32 x 64), with no more than
-    // half of its rows empty; the smallest for its row count otherwise.  Eight waves share a tile:
-    // they are what hides the load latency when the compute unit has no second tile; from one 64 x 64
-    // tile per compute unit on, four (256 x 3072: 12.7 against 14.2 us with eight; 512 x 3072: 21.5
-    // against 23.1 with four).
+    // The largest tile that still gives 0.7 workgroups per compute unit, with no more than half of its
+    // rows empty; the smallest for its row count otherwise.  Decode per flop falls with the tile, but
+    // idle compute units cost more: 128 x 3072 outputs take 9.4 us as 192 tiles of 32 x 64 and over
+    // 10 as 96 of 64 x 64.  Eight waves share a tile: they are what hides the load latency when the
+    // compute unit has no second tile; with more than one 64 x 64 tile per compute unit, four (K = 3072:
+    // 256 x 3072, 192 tiles, 12.7 us with eight and 14.2 with four; 512 x 3072, 384 tiles, 23.1 and 21.5).
     WaveTile t{1, 1, 8};
     const int64_t want = (int64_t)cus * 7 / 10;
     if (M > 32 && tiles(4, 4) >= want) t = WaveTile{4, 4, tiles(4, 4) <= cus ? 8 : 4};
