@@ -89,25 +89,28 @@ __device__ __forceinline__ float dpp_add(float v) {
     return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
-// A workgroup of 256 threads is 16 groups of 16 lanes, a row of Y each; a lane takes every sixteenth
-// chunk (32 codes) of its row and has the loads of up to kRtnBatch of them in flight, all of a row up to
-// K = 3072.  One projection is 29 MB and a few microseconds, so what counts is the chain of latencies in
-// front of the last byte: the weights' loads are issued right behind the tokens' and before anything
-// waits for those, the chunk sums come out of the staging registers (no second barrier), and one row
-// per group spreads 18432 rows over 4.5 workgroups per compute unit instead of 2.25.  Measured, device
-// time: 1 x 3072 -> 18432 11.5 -> 9.6 us (3.2 TB/s; an empty launch is 2.8 us of it), 9216 rows 8.7 -> 7.3,
-// 1 x 5120 -> 60001 37 -> 34, 4 x 5120 -> 40000 54 -> 45 (one pass over the weights instead of two),
-// 1 x 3072 -> 1050624 316 -> 318 (5.4 TB/s).
+// A workgroup of 256 threads is 16 groups of 16 lanes, ROWS rows of Y each; a lane takes every sixteenth
+// chunk (32 codes) of its rows and has the loads of up to six of them in flight, all of a row up to
+// K = 3072.  One projection is 29 MB and a few microseconds, so what counts for one token is the chain of
+// latencies in front of the last byte: the weights' loads are issued right behind the tokens' and before
+// anything waits for those, the chunk sums come out of the staging registers (no second barrier), and one
+// row per group spreads 18432 rows over 4.5 workgroups per compute unit.  Measured, device time of a call in
+// a sequence, against two rows per group staged ahead of the loads: 1 x 3072 -> 18432 9.7 -> 8.1 us (3.7
+// TB/s), 9216 rows 6.9 -> 5.5, 1 x 5120 -> 60001 33.4 -> 29.5, 1 x 3072 -> 1050624 320 -> 313 (5.5 TB/s).
+//
+// Several tokens are bound by the token vectors' LDS reads and the dot products instead: two rows per
+// group read each vector once for both (16 x 3072 -> 18432 43.2 -> 37.6 us).  The launchers below have the
+// choice and its figures.
 constexpr int kRtnLanes = 16;
-constexpr int kRtnBlockRows = 16;
-constexpr int kRtnBatch = 6;
+constexpr int rtn_block_rows(int rows) { return 16 * rows; }
 
 // Persistent: a workgroup stages its tokens once, then walks row blocks blockIdx.x, +gridDim.x, ...
-template <int MT, bool STREAM>
+template <int MT, int ROWS>
 __global__ __launch_bounds__(256) void adaln_int4_linear_kernel(RtnLinearParams p) {
     // The workgroup's MT tokens, paired per 8 as (x0,x4) (x1,x5) (x2,x6) (x3,x7): 16-byte vector t of
     // chunk c sits at t * nchunk + c, so that 16 lanes reading 16 chunks read 256 contiguous bytes
     // (chunk by chunk their vectors would be 64 bytes apart, four to a bank).  Then one fp32 sum per chunk.
+    constexpr int kRtnBlockRows = rtn_block_rows(ROWS), kRtnBatch = 6 / ROWS;
     extern __shared__ __align__(16) uint4 xlds[];
     const int nchunk = p.K / 32, nvec = p.K / 8;
     float* const csum = (float*)(xlds + MT * nvec);
@@ -132,30 +135,33 @@ __global__ __launch_bounds__(256) void adaln_int4_linear_kernel(RtnLinearParams 
 
     const int lane = threadIdx.x & (kRtnLanes - 1), grp = threadIdx.x / kRtnLanes;
     const uint32_t qrow = p.K / 2, srow = p.K / kRtnGroup * 2;  // bytes
-    const uint32_t qoff = grp * qrow + lane * 16, soff = grp * srow + (lane >> 1) * 2;
+    const uint32_t qoff = grp * ROWS * qrow + lane * 16, soff = grp * ROWS * srow + (lane >> 1) * 2;
     const int64_t nblocks = (p.N + kRtnBlockRows - 1) / kRtnBlockRows;
-    u32x4 cw[kRtnBatch];
-    uint16_t sc[kRtnBatch];
+    u32x4 cw[kRtnBatch][ROWS];
+    uint16_t sc[kRtnBatch][ROWS];
     // A batch's loads, through its block's rows as a buffer: rows past the last one read zero, chunks
     // past a row's end the next row's (dropped below), and no address is formed per load.
     struct Batch {
         __amdgpu_buffer_rsrc_t q, s;
-        int c0, slots;  // first chunk, slots of 16 chunks (uniform; 0: there is no such batch)
+        int c0, slots;  // first chunk, slots of 16 chunks (uniform)
     };
     auto batch_at = [&](int64_t blk, int c0) {
         Batch t;
-        const int64_t n0 = min(blk, nblocks - 1) * kRtnBlockRows;
+        const int64_t n0 = blk * kRtnBlockRows;
         const int rows = (int)min((int64_t)kRtnBlockRows, p.N - n0);
         t.q = __builtin_amdgcn_make_buffer_rsrc((void*)(p.q + n0 * qrow), 0, rows * (int)qrow, 0x00027000);
         t.s = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint8_t*)p.scales + n0 * srow), 0, rows * (int)srow, 0x00027000);
         t.c0 = c0;
-        t.slots = blk < nblocks ? min(kRtnBatch, (nchunk - c0 + kRtnLanes - 1) / kRtnLanes) : 0;
+        t.slots = min(kRtnBatch, (nchunk - c0 + kRtnLanes - 1) / kRtnLanes);
         return t;
     };
     auto weight_load = [&](const Batch& t, int b) {
         if (b < t.slots) {
-            cw[b] = __builtin_amdgcn_raw_buffer_load_b128(t.q, qoff + 256 * b, t.c0 * 16, 0);
-            sc[b] = __builtin_amdgcn_raw_buffer_load_b16(t.s, soff + 16 * b, t.c0, 0);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                cw[b][r] = __builtin_amdgcn_raw_buffer_load_b128(t.q, qoff + r * qrow + 256 * b, t.c0 * 16, 0);
+                sc[b][r] = __builtin_amdgcn_raw_buffer_load_b16(t.s, soff + r * srow + 16 * b, t.c0, 0);
+            }
         }
     };
 
@@ -171,106 +177,152 @@ __global__ __launch_bounds__(256) void adaln_int4_linear_kernel(RtnLinearParams 
     for (int i = threadIdx.x + 512; i < total; i += 256) token_store(i, token_load(i));
     __syncthreads();
 
-    auto contract = [&](int b, int c0, float (&tot)[MT]) {
+    auto contract = [&](int b, int c0, float (&tot)[ROWS][MT]) {
         const int c = c0 + lane + kRtnLanes * b, cc = min(c, nchunk - 1);
-        float acc[MT];
+        float acc[ROWS][MT];
 #pragma unroll
-        for (int m = 0; m < MT; ++m) acc[m] = -136.f * csum[m * nchunk + cc];
-        const uint32_t words[4] = {cw[b].x, cw[b].y, cw[b].z, cw[b].w};
+        for (int m = 0; m < MT; ++m) {
+            const float v = -136.f * csum[m * nchunk + cc];
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) acc[r][m] = v;
+        }
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            uint32_t u[4];  // (128 + u_j, 128 + u_{j+4}) of 8 codes, as BF16 pairs
+            uint32_t u[ROWS][4];  // (128 + u_j, 128 + u_{j+4}) of 8 codes, as BF16 pairs
 #pragma unroll
-            for (int j = 0; j < 4; ++j) u[j] = ((words[t] >> (4 * j)) & 0x000F000Fu) | magic;
+            for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) u[r][j] = ((cw[b][r][t] >> (4 * j)) & 0x000F000Fu) | magic;
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
                 const uint4 x = xlds[m * nvec + t * nchunk + cc];
-                acc[m] = dot2(u[0], x.x, acc[m]);
-                acc[m] = dot2(u[1], x.y, acc[m]);
-                acc[m] = dot2(u[2], x.z, acc[m]);
-                acc[m] = dot2(u[3], x.w, acc[m]);
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) {
+                    acc[r][m] = dot2(u[r][0], x.x, acc[r][m]);
+                    acc[r][m] = dot2(u[r][1], x.y, acc[r][m]);
+                    acc[r][m] = dot2(u[r][2], x.z, acc[r][m]);
+                    acc[r][m] = dot2(u[r][3], x.w, acc[r][m]);
+                }
             }
         }
-        const float s = (float)__builtin_bit_cast(_Float16, sc[b]);
 #pragma unroll
-        for (int m = 0; m < MT; ++m) tot[m] = c < nchunk ? fmaf(s, acc[m], tot[m]) : tot[m];
+        for (int r = 0; r < ROWS; ++r) {
+            const float s = (float)__builtin_bit_cast(_Float16, sc[b][r]);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) tot[r][m] = c < nchunk ? fmaf(s, acc[r][m], tot[r][m]) : tot[r][m];
+        }
     };
     for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
-        float tot[MT];
+        float tot[ROWS][MT];
 #pragma unroll
-        for (int m = 0; m < MT; ++m) tot[m] = 0.f;
+        for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) tot[r][m] = 0.f;
         for (int c0 = 0; c0 < nchunk; c0 += kRtnLanes * kRtnBatch) {
-            if constexpr (STREAM) {
-                // the next batch, of this row or of the next block's: its loads take each slot's registers
-                // as soon as they are free, so that as much is in flight in every round as in the first
-                const Batch next = c0 + kRtnLanes * kRtnBatch < nchunk ? batch_at(blk, c0 + kRtnLanes * kRtnBatch)
-                                                                       : batch_at(blk + gridDim.x, 0);
+            if (c0 > 0 || blk != blockIdx.x) {
+                cur = batch_at(blk, c0);
 #pragma unroll
-                for (int b = 0; b < kRtnBatch; ++b) {
-                    if (b < cur.slots) contract(b, c0, tot);  // (uniform)
-                    weight_load(next, b);
-                    __builtin_amdgcn_sched_barrier(0);  // one chunk's token reads at a time (registers)
-                }
-                cur = next;
-            } else {
-                if (c0 > 0 || blk != blockIdx.x) {
-                    cur = batch_at(blk, c0);
+                for (int b = 0; b < kRtnBatch; ++b) weight_load(cur, b);
+            }
 #pragma unroll
-                    for (int b = 0; b < kRtnBatch; ++b) weight_load(cur, b);
-                }
-#pragma unroll
-                for (int b = 0; b < kRtnBatch; ++b) {
-                    if (c0 + kRtnLanes * b >= nchunk) break;  // uniform: no chunk of this slot exists
-                    contract(b, c0, tot);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+            for (int b = 0; b < kRtnBatch; ++b) {
+                if (c0 + kRtnLanes * b >= nchunk) break;  // uniform: no chunk of this slot exists
+                contract(b, c0, tot);
+                __builtin_amdgcn_sched_barrier(0);  // one chunk's token reads at a time (registers)
             }
         }
 
         // fixed-order sum over the 16 lanes of the group (one DPP row): pairs, quads, 8, 16
-        const int64_t n = blk * kRtnBlockRows + grp;
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            float v = tot[m];
-            v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
-            v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
-            v = dpp_add<0x141>(v);  // row_half_mirror
-            v = dpp_add<0x140>(v);  // row_mirror
-            if (lane == 0 && n < p.N && m0 + m < p.M) {
-                if (p.bias) v += __uint_as_float((uint32_t)p.bias[n] << 16);
-                p.Y[(int64_t)(m0 + m) * p.ldy + n] = v;
+        for (int r = 0; r < ROWS; ++r) {
+            const int64_t n = blk * kRtnBlockRows + grp * ROWS + r;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                float v = tot[r][m];
+                v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
+                v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
+                v = dpp_add<0x141>(v);  // row_half_mirror
+                v = dpp_add<0x140>(v);  // row_mirror
+                if (lane == 0 && n < p.N && m0 + m < p.M) {
+                    if (p.bias) v += __uint_as_float((uint32_t)p.bias[n] << 16);
+                    p.Y[(int64_t)(m0 + m) * p.ldy + n] = v;
+                }
             }
         }
     }
 }
 
-template <int MT, bool STREAM>
-hipError_t launch_grid(const RtnLinearParams& p, unsigned gx, hipStream_t stream) {
-    const size_t lds = (size_t)MT * (p.K / 8) * sizeof(uint4) + (size_t)MT * (p.K / 32) * sizeof(float);
-    if (lds > 64 * 1024) {
-        static std::atomic<uint64_t> attr{0};
-        const hipError_t e = raise_lds_limit((const void*)adaln_int4_linear_kernel<MT, STREAM>, 160 * 1024, attr);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((adaln_int4_linear_kernel<MT, STREAM>), dim3(gx, (unsigned)((p.M + MT - 1) / MT)), dim3(256), lds,
-                       stream, p);
+// LDS of a workgroup that stages mt tokens
+size_t rtn_lds(int mt, int K) { return (size_t)mt * ((size_t)K / 8 * sizeof(uint4) + (size_t)K / 32 * sizeof(float)); }
+
+int64_t rtn_blocks(int64_t N, int rows) { return (N + rtn_block_rows(rows) - 1) / rtn_block_rows(rows); }
+
+template <int MT, int ROWS>
+hipError_t raise_rtn_lds(int K) {
+    static std::atomic<uint64_t> attr{0};
+    return rtn_lds(MT, K) > 64 * 1024 ? raise_lds_limit((const void*)adaln_int4_linear_kernel<MT, ROWS>, 160 * 1024, attr)
+                                      : hipSuccess;
+}
+
+// Workgroups walk the row blocks, the same number of blocks each as far as that goes: at most `per_cu` of
+// them per compute unit.
+struct RtnGrid {
+    int64_t workgroups, rounds;
+};
+RtnGrid rtn_grid(int64_t N, int rows, int per_cu, int cus) {
+    const int64_t blocks = rtn_blocks(N, rows), most = (int64_t)per_cu * cus, rounds = (blocks + most - 1) / most;
+    return RtnGrid{(blocks + rounds - 1) / rounds, rounds};
+}
+
+template <int MT, int ROWS>
+hipError_t launch_linear(const RtnLinearParams& p, int per_cu, int cus, hipStream_t stream) {
+    const hipError_t e = raise_rtn_lds<MT, ROWS>(p.K);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)rtn_grid(p.N, ROWS, per_cu, cus).workgroups, (unsigned)((p.M + MT - 1) / MT));
+    hipLaunchKernelGGL((adaln_int4_linear_kernel<MT, ROWS>), grid, dim3(256), rtn_lds(MT, p.K), stream, p);
     return hipGetLastError();
 }
 
-template <int MT>
-hipError_t launch_linear(const RtnLinearParams& p, int cus, hipStream_t stream) {
-    // Workgroups walk the row blocks, the same number of blocks each as far as that goes: six per compute
-    // unit, where their waves cover each other's latencies.  One token against hundreds of thousands of
-    // rows (a step's projections in one call) is a long stream instead: eight leaner ones with the next
-    // rows' loads always in flight (1050624 x 3072: 318 against 350 us; 60001 x 5120: 37 against 33).
-    const int64_t nblocks = (p.N + kRtnBlockRows - 1) / kRtnBlockRows;
-    const bool stream_rows = MT == 1 && nblocks > (int64_t)48 * cus;
-    // (two tokens take 160 registers: three workgroups are what a compute unit holds)
-    const int64_t most = (int64_t)(stream_rows ? 8 : MT == 2 && nblocks > (int64_t)6 * cus ? 3 : 6) * cus, rounds = (nblocks + most - 1) / most;
-    const unsigned gx = (unsigned)((nblocks + rounds - 1) / rounds);
-    if constexpr (MT == 1)
-        if (stream_rows) return launch_grid<1, true>(p, gx, stream);
-    return launch_grid<MT, false>(p, gx, stream);
+// One token: six workgroups per compute unit, where their waves cover each other's latencies.  One row per
+// group while that grid is resident at once (3072 -> 18432: 8.1 us, two rows 10.7), or where it splits the
+// rows more evenly over the compute units (3072 -> 73728: 21.8 and 22.6); two rows otherwise (5120 ->
+// 30720: 18.4 -> 17.8, 8192 -> 65536: 55.4 -> 50.9), and from four workgroups per compute unit on where a
+// row's chunks fill at most half of the six loads (512 -> 18432: 4.2 -> 3.7).  Hundreds of thousands of
+// rows (a step's projections in one call) want fewer, longer walks: three workgroups per compute unit
+// (3072 -> 1050624: 313 us, 320 with six).  Where the token leaves LDS for four workgroups only, two rows
+// never pay (16384 -> 30720: 52 us, 59) and longer grids are of four (16384 -> 65536: 119 -> 110).
+hipError_t launch_one_token(const RtnLinearParams& p, int cus, hipStream_t stream) {
+    const int64_t blocks = rtn_blocks(p.N, 1);
+    if (5 * rtn_lds(1, p.K) > 160 * 1024) return launch_linear<1, 1>(p, blocks <= (int64_t)6 * cus ? 6 : 4, cus, stream);
+    if (blocks > (int64_t)48 * cus) return launch_linear<1, 2>(p, 3, cus, stream);
+    auto busiest = [&](int rows) {  // rows of the busiest compute unit
+        const RtnGrid g = rtn_grid(p.N, rows, 6, cus);
+        return (g.workgroups + cus - 1) / cus * g.rounds * rtn_block_rows(rows);
+    };
+    const bool resident = blocks <= (int64_t)(p.K <= 1024 ? 4 : 6) * cus;
+    if (resident || (p.K > 1024 && busiest(1) < busiest(2))) return launch_linear<1, 1>(p, 6, cus, stream);
+    return launch_linear<1, 2>(p, 6, cus, stream);
+}
+
+// Several tokens: two or four a pass over the weights (at 150 registers, three workgroups per compute unit).
+// One row per group where that grid is resident at once, as the latencies decide there (4 x 3072 -> 12288:
+// 10.1 us, two rows 11.1; 2 x 3072 -> 9216: 7.2 and 7.7), two where workgroups queue (8 x 3072 -> 18432:
+// 23.9 -> 22.5; 101 x 5120 -> 40000: 775 -> 687).  Four tokens a pass except where
+//   - the last pass would be half empty: 5 and 6 tokens (3072 -> 18432: 21.4 us two at a time, 23.4 four);
+//   - two at a time still fit twice per compute unit (4 x 5120 -> 2048: 7.0 us, 9.4);
+//   - four tokens leave LDS for fewer than three workgroups (16 x 16384 -> 18432: 282 us, 335).
+hipError_t launch_tokens(const RtnLinearParams& p, int cus, hipStream_t stream) {
+    hipError_t e = raise_rtn_lds<2, 1>(p.K);
+    if (e == hipSuccess) e = raise_rtn_lds<4, 1>(p.K);
+    if (e != hipSuccess) return e;
+    const int64_t blocks = rtn_blocks(p.N, 1), wgs2 = blocks * ((p.M + 1) / 2), wgs4 = blocks * ((p.M + 3) / 4);
+    const bool four = p.M > 2 && p.M != 5 && p.M != 6;
+    const int fit2 = resident_blocks((const void*)adaln_int4_linear_kernel<2, 1>, 256, rtn_lds(2, p.K));
+    const int fit4 = resident_blocks((const void*)adaln_int4_linear_kernel<4, 1>, 256, rtn_lds(4, p.K));
+    if (wgs2 <= (int64_t)(four ? std::min(2, fit2) : fit2) * cus) return launch_linear<2, 1>(p, 3, cus, stream);
+    if (four && wgs4 <= (int64_t)fit4 * cus) return launch_linear<4, 1>(p, 4, cus, stream);
+    if (four && 3 * rtn_lds(4, p.K) <= 160 * 1024) return launch_linear<4, 2>(p, 3, cus, stream);
+    return launch_linear<2, 2>(p, 3, cus, stream);
 }
 
 }  // namespace
@@ -285,10 +337,7 @@ hipError_t launch_adaln_int4_quantize(const uint16_t* W, int64_t N, int K, int64
 }
 
 hipError_t launch_adaln_int4_linear(const RtnLinearParams& p, int cus, hipStream_t stream) {
-    // one pass over the weights per four tokens, or two where four would leave half a pass empty
-    if (p.M == 1) return launch_linear<1>(p, cus, stream);
-    if (p.M % 4 == 1 || p.M % 4 == 2) return launch_linear<2>(p, cus, stream);
-    return launch_linear<4>(p, cus, stream);
+    return p.M == 1 ? launch_one_token(p, cus, stream) : launch_tokens(p, cus, stream);
 }
 
 }  // namespace orbit

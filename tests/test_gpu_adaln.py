@@ -10,6 +10,7 @@ import torch
 import oracle
 import paper_2607_02461_amd as oq
 from paper_2607_02461_amd import workloads
+from paper_2607_02461_amd.launches import launches
 from tests.gpu_util import GEMM_REL_F, log_stats, rel_frobenius, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -87,10 +88,48 @@ def test_linear_strided_input_and_padded_output():
     assert not torch.isnan(out).any()
 
 
-# long streams: one token against more than 48 row blocks of 16 per compute unit (196608 rows on 256), with
-# the next rows' loads in flight across blocks; whole and ragged blocks, one and two batches of chunks, a
-# partial slot of chunks; the same rows in two short calls give the same bits
-@pytest.mark.parametrize("M,N,K", [(1, 200000, 128), (1, 197007, 3136), (2, 100001, 192), (4, 50001, 1600)])
+# Tokens per pass and rows per 16 lanes follow from the sizes (256 compute units): two or four tokens, one row
+# or two.  Ragged row blocks of 16 and 32, passes with one to three tokens missing, part of a batch of chunks;
+# whichever way a call goes, every token's outputs are the bits of a call of its own.
+@pytest.mark.parametrize("M,N,K,kernel", [(4, 1000, 3072, "<2,1>"), (2, 9001, 1600, "<2,1>"), (3, 12289, 1088, "<4,1>"),
+                                          (7, 8001, 1088, "<4,1>"), (2, 18433, 1088, "<2,2>"), (5, 9217, 64, "<2,2>"),
+                                          (6, 9217, 1600, "<2,2>"), (3, 18449, 128, "<4,2>"), (8, 9233, 1088, "<4,2>"),
+                                          (9, 9233, 192, "<4,2>"), (4, 9001, 16384, "<2,2>")])
+def test_tokens_of_a_pass(M, N, K, kernel):
+    W = _weights(N, K, seed=M + N + K)
+    q, s = oq.adaln_int4_quantize_weights(W)
+    X = workloads.adaln_tokens(M, K, seed=M + K, device=DEV)
+    out = torch.full((M, N + 3), float("nan"), device=DEV)
+    Y = oq.adaln_int4_linear(X, q, s, out=out[:, :N])
+    each = torch.cat([oq.adaln_int4_linear(X[m:m + 1], q, s) for m in range(M)])
+    torch.cuda.synchronize()
+    assert torch.equal(Y, each) and bool(torch.isnan(out[:, N:]).all())
+    rows = torch.tensor([0, 1, 15, 16, 31, 32, N // 2, N - 17, N - 2, N - 1], device=DEV)
+    oqq, osc = oracle.rtn_int4_quantize(to_f64(W[rows]))
+    ref = oracle.rtn_int4_linear(to_f64(X), oqq, osc)
+    assert rel_frobenius(Y[:, rows].double().cpu().numpy(), ref) <= GEMM_REL_F
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        ran, = launches(lambda: oq.adaln_int4_linear(X, q, s, out=out[:, :N]))
+        assert ran.kernel == "adaln_int4_linear_kernel" + kernel
+
+
+def test_weights_stream_once_per_four_tokens():
+    # however many tokens are left over, the rows of q and the scales are read once per four of them (once per
+    # two for 5 and 6), on any device
+    N, K = 18432, 3072
+    q, s = torch.zeros((N, K // 2), dtype=torch.uint8, device=DEV), torch.zeros((N, K // 64), dtype=torch.float16, device=DEV)
+    for M, passes in ((1, 1), (4, 1), (9, 3), (10, 3), (33, 9), (101, 26), (102, 26)):
+        X, Y = torch.zeros((M, K), dtype=torch.bfloat16, device=DEV), torch.empty((M, N), device=DEV)
+        ran, = launches(lambda: oq.adaln_int4_linear(X, q, s, out=Y))
+        assert ran.grid[1] == passes, f"{M} tokens take {ran.grid[1]} passes over the weights"
+
+
+# one token: a row of a group of 16 lanes or two (short rows, grids beyond six workgroups per compute unit),
+# walks of many blocks (from 196608 rows on 256 compute units on); several tokens on long walks; whole and
+# ragged blocks, one and two batches of chunks, a partial slot of chunks; the same rows in two short calls give
+# the same bits
+@pytest.mark.parametrize("M,N,K", [(1, 200000, 128), (1, 197007, 3136), (1, 16401, 192), (1, 30721, 1600), (1, 24593, 16384),
+                                   (2, 100001, 192), (4, 50001, 1600)])
 def test_long_streams(M, N, K):
     W = _weights(N, K, seed=N)
     q, s = oq.adaln_int4_quantize_weights(W)
