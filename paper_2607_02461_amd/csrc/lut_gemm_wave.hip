@@ -26,10 +26,11 @@ namespace orbit {
 
 namespace {
 
-constexpr int KC = 128;  // inputs per chunk: 32 codes of a row per lane
+constexpr int KC = 128;    // inputs per chunk: 32 codes of a row per lane
+constexpr int kWaves = 8;  // at most, of a workgroup
 
 template <int BA, int BW, int MT, int NT, int DEPTH>
-__global__ __launch_bounds__(MT * NT >= 16 ? 512 : 1024) void lut_gemm_wave(GemmParams p) {
+__global__ __launch_bounds__(64 * kWaves) void lut_gemm_wave(GemmParams p) {
     extern __shared__ __align__(16) unsigned char lds[];  // [wave][16 MT][16 NT + 4] fp32 sums; then the 6-bit table
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x >> 6;
@@ -150,7 +151,10 @@ hipError_t launch_wave(const GemmParams& p, const WaveTile& t, hipStream_t strea
     }
     if (t.mt == 2) {
         if (t.nt == 2) return launch_tile<BA, BW, 2, 2, 2>(p, t.waves, stream);
-        return launch_tile<BA, BW, 2, 4, 2>(p, t.waves, stream);
+        // two chunks of 6-bit codes in flight are over 128 registers: spills with two workgroups on a compute
+        // unit, or only one there (128 x 3072 x 3072 W4A6: 16.7 us spilling, 13.2 alone, 12.5 with one chunk;
+        // 128 x 5120 x 1536: 16.2, 16.3, 11.3)
+        return launch_tile<BA, BW, 2, 4, BA == 6 ? 1 : 2>(p, t.waves, stream);
     }
     if (t.waves > 4) return launch_tile<BA, BW, 4, 4, 1>(p, t.waves, stream);
     return launch_tile<BA, BW, 4, 4, 2>(p, t.waves, stream);
@@ -166,11 +170,11 @@ WaveTile lut_gemm_wave_tile(int64_t M, int64_t N, int64_t K, int cus) {
     // 10 as 96 of 64 x 64.  Eight waves share a tile: they are what hides the load latency when the
     // compute unit has no second tile; with more than one 64 x 64 tile per compute unit, four (K = 3072:
     // 256 x 3072, 192 tiles, 12.7 us with eight and 14.2 with four; 512 x 3072, 384 tiles, 23.1 and 21.5).
-    WaveTile t{1, 1, 8};
+    WaveTile t{1, 1, kWaves};
     const int64_t want = (int64_t)cus * 7 / 10;
-    if (M > 32 && tiles(4, 4) >= want) t = WaveTile{4, 4, tiles(4, 4) <= cus ? 8 : 4};
-    else if (M > 16) t = WaveTile{2, tiles(2, 4) >= want ? 4 : 2, 8};
-    else if (tiles(1, 4) >= want) t = WaveTile{1, 4, 8};
+    if (M > 32 && tiles(4, 4) >= want) t = WaveTile{4, 4, tiles(4, 4) <= cus ? kWaves : kWaves / 2};
+    else if (M > 16) t = WaveTile{2, tiles(2, 4) >= want ? 4 : 2, kWaves};
+    else if (tiles(1, 4) >= want) t = WaveTile{1, 4, kWaves};
     t.waves = (int)std::min<int64_t>(t.waves, K / KC);
     return t;
 }
