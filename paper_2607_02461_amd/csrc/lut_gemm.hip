@@ -730,22 +730,32 @@ __global__ __launch_bounds__(256) void lut_gemm_reduce(GemmParams p, int splits)
     }
 }
 
-// The kernel for rows that do not fill the device with large tiles.  Estimated microseconds of each,
-// within 15% of 60 measured shapes (M 1 .. 20000, N 768 .. 15360, K 1024 .. 16384, four bit pairs, on
-// 256 compute units); a tie stays on the 128 x 128 kernel.
+// The kernel for rows that do not fill the device with large tiles, by an estimate of each one's
+// microseconds.  Fitted to 1600 layers timed on all three (M 1 .. 8000, N 96 .. 18432, K 256 .. 16384, every
+// bit pair, 256 compute units): nine in ten estimates within 14%, and where rows are not stored in
+// vectors (N or ldy not a multiple of 4) four in five within 20%.  The choice costs 0.1% over the
+// fastest kernel on average, 19% at worst; 9 of 2986 calls (each layer with a workspace and without) are
+// over 3% slower than on 128 x 128 tiles, the worst 13%.  A tie stays on the 128 x 128 kernel.
 enum class Kernel { kSmall, kWave, kLarge };
 
-Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int splits, int split_steps, int cus) {
+Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int splits, int split_steps, bool vectors,
+                      int cus) {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     // decode cost relative to 4-bit codes, per operand: 1.3 at 3 bits, 1.85 at 6
     auto cost = [](int b) { return b == 3 ? 1.3 : b == 6 ? 1.85 : 1.0; };
     const double f = 0.5 * (cost(ba) + cost(bw)), steps = (double)(K / BK);
     // 128 x 128: k co-resident workgroups per compute unit take 0.58, 1.03, 1.64 and 2.13 us per K-step
-    // for k = 1 .. 4, 0.48 us each beyond; splitting adds the partial sums' round trip and the reduction
+    // for k = 1 .. 4, 0.48 us each beyond.  A split costs the reduction 0.23 us (its threads walk the
+    // splits one by one) and its sums' round trip at 5.3 TB/s; element by element, 0.49 us and 1.7
+    // TB/s (156 x 385 x 13824 W4A4 in 31 splits: 44.8 us, 18.0 on wave tiles).  Without a split, stores element by
+    // element add 9 us for each further workgroup.
     const int64_t wgs = tiles(BM, BN) * splits, k = (wgs + cus - 1) / cus;
     const double step = k == 1 ? 0.58 : k == 2 ? 1.03 : k == 3 ? 1.64 : k == 4 ? 2.13 : 0.48 * (double)wgs / cus;
-    double best = 0.95 * (7.5 + step * (0.25 + 0.75 * f) * (splits > 1 ? (double)split_steps : steps) +
-                          (splits > 1 ? 2.0 + (double)splits * (double)M * (double)N * 8.0 / 4.2e6 : 0.0));
+    const double more = (double)(k - 1), sums = (double)splits * (double)M * (double)N * 8e-6;  // MB
+    double best;
+    if (splits > 1 && vectors) best = 6.4 + 0.45 * more + step * f * split_steps + 0.23 * splits + 0.19 * sums;
+    else if (splits > 1) best = 7.3 + 0.9 * step * f * split_steps + 0.49 * splits + 0.6 * sums;
+    else best = (vectors ? 6.4 + 0.45 * more : 9.5 + 9.0 * more) + step * f * steps;
     Kernel kernel = Kernel::kSmall;
     // 256 x 256, one round: 1.27 us per K-step while up to 0.6 of the compute units have a tile, 1.52 us
     // when all do (the clock falls).  4429 x 3072 x 3072 W3A3: 85 us against 129 on 128 x 128 tiles;
@@ -753,18 +763,20 @@ Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int split
     const int64_t large = tiles(BM2, BN2);
     if (large <= cus && K <= MAX_K2) {
         const double full = std::max(0.0, (double)large / cus - 0.6) / 0.4;
-        const double t = 10.0 + steps * (1.27 + 0.25 * full) * (0.5 + 0.5 * f);
+        const double t = (vectors ? 10.0 : 22.0) + steps * (1.27 + 0.25 * full) * (0.5 + 0.5 * f);
         if (t < best) {
             best = t;
             kernel = Kernel::kLarge;
         }
     }
-    // wave tiles, whole chunks of 128 only: the busiest compute unit's tiles, 0.346 us per
-    // 64 x 64 x 128 chunk, others in proportion to their decode
+    // wave tiles, whole chunks of 128 only: the busiest compute unit's tiles, 1.2 us for a 64 x 64 one and
+    // 0.34 us for each of its chunks, others 0.3 in proportion to their decode.  (Without the cost of a
+    // tile, short contractions went here wrongly: 1319 x 5120 x 640 W4A2 27.4 us, 20.2 on 128 x 128 tiles.)
     if (K % 128 == 0 && (M + 15) / 16 <= 65535) {
         const WaveTile w = lut_gemm_wave_tile(M, N, K, cus);
-        const int64_t per_cu = (tiles(16 * w.mt, 16 * w.nt) + cus - 1) / cus;
-        const double t = 4.5 + (double)per_cu * (double)(K / 128) * 0.346 * f * (w.mt + w.nt) / 8.0;
+        const double per_cu = (double)((tiles(16 * w.mt, 16 * w.nt) + cus - 1) / cus) * (w.mt + w.nt) / 8.0;
+        const bool whole = w.mt == 4 && w.nt == 4;
+        const double t = 3.3 + per_cu * ((whole ? 1.2 : 0.0) + (whole ? 0.34 : 0.3) * f * (double)(K / 128));
         if (t < best) kernel = Kernel::kWave;
     }
     return kernel;
@@ -772,7 +784,7 @@ Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int split
 
 template <int BA, int BW>
 hipError_t launch_small(const GemmParams& p, hipStream_t stream, int cus) {
-    switch (fastest_kernel(p.M, p.N, p.K, BA, BW, p.ws ? p.splits : 1, p.split_steps, cus)) {
+    switch (fastest_kernel(p.M, p.N, p.K, BA, BW, p.ws ? p.splits : 1, p.split_steps, p.vec4 && p.N % 4 == 0, cus)) {
         case Kernel::kWave: return launch_lut_gemm_wave(p, BA, BW, cus, stream);
         case Kernel::kLarge: return launch_big<BA, BW>(p, stream);
         default: break;
