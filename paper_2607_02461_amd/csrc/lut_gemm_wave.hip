@@ -151,10 +151,11 @@ hipError_t launch_wave(const GemmParams& p, const WaveTile& t, hipStream_t strea
     }
     if (t.mt == 2) {
         if (t.nt == 2) return launch_tile<BA, BW, 2, 2, 2>(p, t.waves, stream);
-        // two chunks of 6-bit codes in flight are over 128 registers: spills with two workgroups on a compute
-        // unit, or only one there (128 x 3072 x 3072 W4A6: 16.7 us spilling, 13.2 alone, 12.5 with one chunk;
-        // 128 x 5120 x 1536: 16.2, 16.3, 11.3)
-        return launch_tile<BA, BW, 2, 4, BA == 6 ? 1 : 2>(p, t.waves, stream);
+        // two chunks of 6-bit codes in flight, beside 3- or 4-bit ones, are over 128 registers: spills with two
+        // workgroups on a compute unit, or only one there (128 x 3072 x 3072 W4A6: 16.7 us spilling, 13.2
+        // alone, 12.5 with one chunk; 128 x 5120 x 1536: 16.2, 16.3, 11.3).  Beside 2-bit codes two fit (118
+        // registers; 18 x 12288 x 12288 W2A6: 33.3 us, 35.7 with one).
+        return launch_tile<BA, BW, 2, 4, (BA == 6 && BW > 2) ? 1 : 2>(p, t.waves, stream);
     }
     if (t.waves > 4) return launch_tile<BA, BW, 4, 4, 1>(p, t.waves, stream);
     return launch_tile<BA, BW, 4, 4, 2>(p, t.waves, stream);

@@ -16,3 +16,5 @@ def test_wave_kernel_keeps_its_loop_in_registers():
         assert k[".max_flat_workgroup_size"] == 512, name
         if re.match(r"lut_gemm_wave<\d,\d,2,4,", name):
             assert k[".vgpr_count"] <= 128, f"{name} takes {k['.vgpr_count']} registers"
+    # the 32 x 64 tile has two chunks of codes in flight wherever they fit those registers
+    assert {n for n in kernels if re.match(r"lut_gemm_wave<\d,\d,2,4,1", n)} == {"lut_gemm_wave<6,3,2,4,1>", "lut_gemm_wave<6,4,2,4,1>"}
