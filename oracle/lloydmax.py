@@ -17,6 +17,7 @@ unique and does not depend on the start.
 """
 
 from dataclasses import dataclass
+from functools import lru_cache
 
 import numpy as np
 
@@ -51,9 +52,26 @@ def lloydmax_codebook(bits: int, d: int, start=None, tol: float = 1e-15, max_ite
     about delta * rho / (1 - rho); iteration stops when that estimate, in units
     of 1/sqrt(d), is below tol, or when the step stops shrinking for 200
     iterations (the fp64 rounding floor has been reached).
+
+    Codebooks from the default start are kept for the life of the process (read-only arrays): one
+    of 6 bits takes seconds.
     """
     if bits < 1 or d < 3:
         raise ValueError("need bits >= 1 and d >= 3")
+    if start is None:
+        return _from_default_start(bits, d, tol, max_iter)
+    return _iterate(bits, d, start, tol, max_iter)
+
+
+@lru_cache(maxsize=None)
+def _from_default_start(bits: int, d: int, tol: float, max_iter: int) -> Codebook:
+    cb = _iterate(bits, d, None, tol, max_iter)
+    cb.levels.setflags(write=False)
+    cb.thresholds.setflags(write=False)
+    return cb
+
+
+def _iterate(bits: int, d: int, start, tol: float, max_iter: int) -> Codebook:
     n = 1 << bits
     sd = 1.0 / np.sqrt(d)
     if start is None:
