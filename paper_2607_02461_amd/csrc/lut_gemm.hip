@@ -738,12 +738,12 @@ __global__ __launch_bounds__(256) void lut_gemm_reduce(GemmParams p, int splits)
 // over 3% slower than on 128 x 128 tiles, the worst 13%.  A tie stays on the 128 x 128 kernel.
 enum class Kernel { kSmall, kWave, kLarge };
 
-Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int splits, int split_steps, bool vectors,
-                      int cus) {
+Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int splits, int split_steps, int cus) {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     // decode cost relative to 4-bit codes, per operand: 1.3 at 3 bits, 1.85 at 6
     auto cost = [](int b) { return b == 3 ? 1.3 : b == 6 ? 1.85 : 1.0; };
     const double f = 0.5 * (cost(ba) + cost(bw)), steps = (double)(K / BK);
+    const bool vectors = N % 4 == 0;
     // 128 x 128: k co-resident workgroups per compute unit take 0.58, 1.03, 1.64 and 2.13 us per K-step
     // for k = 1 .. 4, 0.48 us each beyond.  A split costs the reduction 0.23 us (its threads walk the
     // splits one by one) and its sums' round trip at 5.3 TB/s; element by element, 0.49 us and 1.7
@@ -784,7 +784,7 @@ Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int split
 
 template <int BA, int BW>
 hipError_t launch_small(const GemmParams& p, hipStream_t stream, int cus) {
-    switch (fastest_kernel(p.M, p.N, p.K, BA, BW, p.ws ? p.splits : 1, p.split_steps, p.vec4 && p.N % 4 == 0, cus)) {
+    switch (fastest_kernel(p.M, p.N, p.K, BA, BW, p.ws ? p.splits : 1, p.split_steps, cus)) {
         case Kernel::kWave: return launch_lut_gemm_wave(p, BA, BW, cus, stream);
         case Kernel::kLarge: return launch_big<BA, BW>(p, stream);
         default: break;

@@ -10,6 +10,7 @@ import torch
 import oracle
 import paper_2607_02461_amd as oq
 from paper_2607_02461_amd import workloads
+from paper_2607_02461_amd.launches import launches
 from tests.gpu_util import (GEMM_REL_F, check_gemm, gemm_scale, log_stats, near_tie_flip_bound, qlinear_oracle_bf16,
                             rel_frobenius, to_f64)
 
@@ -42,11 +43,12 @@ def _gpu(xc, xs, wc, wr, ba, bw, K):
     return Y.cpu().numpy().astype(np.float64)
 
 
-# the 128 x 128 kernel keeps the codes of 5 K-steps in flight in 6 register sets: step counts 1, 2,
-# 3, 4, 5, 7, 8, 9, 48, 216 cover no full round of that ring, whole rounds and each remainder
+# small grids: with K a multiple of 128 on wave tiles, otherwise on the 128 x 128 kernel, which keeps the
+# codes of 5 K-steps in flight in 6 register sets: its step counts 1, 3, 5, 7, 9 and 11 here and the even
+# ones of the next test cover no full round of that ring, one, and each remainder
 @pytest.mark.parametrize("M,N,K", [(1, 128, 64), (257, 384, 256), (300, 130, 512), (64, 3072, 3072),
                                    (129, 257, 13824), (5, 1, 128), (70, 96, 320), (33, 200, 448),
-                                   (40, 200, 192), (40, 200, 576)])
+                                   (40, 200, 192), (40, 200, 576), (40, 200, 704)])
 @pytest.mark.parametrize("ba,bw", [(4, 4), (4, 3), (4, 2), (3, 3), (2, 2), (3, 4), (2, 4), (6, 4), (6, 3), (6, 2)])
 def test_random_codes(M, N, K, ba, bw):
     xc, xs, wc, wr = _inputs(M, N, K, ba, bw, seed=M + N + K)
@@ -55,14 +57,31 @@ def test_random_codes(M, N, K, ba, bw):
     check_gemm(f"gemm random M={M} N={N} K={K} W{bw}A{ba}", Y, qlinear_oracle_bf16(*args), _scale(*args), K)
 
 
+# the 128 x 128 kernel on even step counts: grids where wave tiles would be slower (on 256 compute units)
+@pytest.mark.parametrize("M,N,K", [(201, 9216, 128), (201, 9216, 256), (1570, 2048, 384), (1570, 2048, 512),
+                                   (1570, 2048, 640)])
+@pytest.mark.parametrize("ba,bw", [(4, 4), (4, 3), (2, 2), (3, 4), (6, 4), (6, 2)])
+def test_random_codes_even_step_counts(M, N, K, ba, bw):
+    xc, xs, wc, wr = _inputs(M, N, K, ba, bw, seed=M + N + K)
+    Y = _gpu(xc, xs, wc, wr, ba, bw, K)
+    args = (xc.numpy(), xs.double().numpy(), ba, wc.numpy(), wr.double().numpy(), bw, K)
+    check_gemm(f"gemm even steps M={M} N={N} K={K} W{bw}A{ba}", Y, qlinear_oracle_bf16(*args), _scale(*args), K)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        cba, cbw = oq.lloydmax_codebook(ba, K), oq.lloydmax_codebook(bw, K)
+        xp, wp = (torch.zeros((r, K * b // 8), dtype=torch.uint8, device=DEV) for r, b in ((M, ba), (N, bw)))
+        norms, out = (xs.to(DEV), wr.to(DEV)), torch.empty((M, N), device=DEV)
+        ran = launches(lambda: oq.orbit_qlinear(cba, xp, norms[0], cbw, wp, norms[1], out=out))
+        assert [r.kernel for r in ran] == [f"lut_gemm_kernel<{ba},{bw},false>"]
+
+
 # shapes with at least one 256x256 tile per compute unit (256) run the large-tile kernel; these
 # cover its ragged edges in M and N, a single K-step, an odd number of K-steps and a grid of
 # under two tiles per compute unit (289).  On 256 compute units the first four leave a last round
-# that is mostly empty, so the large kernel takes the rows of its full rounds and the 128x128
-# kernel the rest (shifted operands and output, ragged in M and N); 3900 x 8000 fills exactly two
+# that is mostly empty, so the large kernel takes the rows of its full rounds and another kernel (128x128
+# tiles, or wave tiles) the rest (shifted operands and output, ragged in M and N); 3900 x 8000 fills exactly two
 # rounds (16 x 32 tiles) and runs the large kernel alone, ragged in both.
-# K-step counts 1, 2, 3, 4, 5, 16 cover the large kernel's three-set code ring: no full round, whole
-# rounds, and each length of the remainder
+# K-step counts 1, 2, 3, 4, 5, 16 cover the large kernel's ring of four code sets: no full round, whole
+# rounds, and remainders
 @pytest.mark.parametrize("M,N,K", [(4133, 8061, 64), (4133, 8061, 128), (4133, 8061, 192), (4133, 8061, 256),
                                    (8197, 4099, 1024), (4133, 4099, 320), (3900, 8000, 192)])
 @pytest.mark.parametrize("ba,bw", [(4, 4), (4, 3), (2, 2), (3, 4), (6, 4), (6, 2)])
@@ -88,10 +107,11 @@ def test_random_codes_partial_round_of_large_tiles(M, N, K, ba, bw):
     check_gemm(f"gemm partial round M={M} N={N} K={K} W{bw}A{ba}", Y, qlinear_oracle_bf16(*args), _scale(*args), K)
 
 
-# the fused layer epilogue (bias, GELU, bf16 output) on both kernels, with vector and element-wise
-# stores (ldy a multiple of 4 or not); with N and ldy multiples of 4 the outputs go through the
-# kernels' LDS turn-around
-@pytest.mark.parametrize("M,N,K", [(300, 130, 512), (4133, 8061, 192), (300, 132, 512), (4133, 8064, 192)])
+# the fused layer epilogue (bias, GELU, bf16 output) on all three kernels (K = 512: wave tiles, 576: 128 x 128
+# tiles), with vector and element-wise stores (ldy a multiple of 4 or not); with N and ldy multiples of 4
+# the outputs of the two larger ones go through their LDS turn-around
+@pytest.mark.parametrize("M,N,K", [(300, 130, 512), (4133, 8061, 192), (300, 132, 512), (4133, 8064, 192),
+                                   (300, 130, 576), (300, 132, 576)])
 @pytest.mark.parametrize("bias,gelu,bf16", [(True, False, False), (False, True, False), (False, False, True),
                                             (True, True, True)])
 @pytest.mark.parametrize("pad", [0, 1])
@@ -246,9 +266,10 @@ def test_binding_rejects_bad_operands():
 
 
 @pytest.mark.parametrize("ba,bw", [(4, 4), (2, 3)])
-def test_long_contraction(ba, bw):
-    # K = 65536 (1024 K-steps of fp32 accumulation) on the 128 x 128 kernel, all outputs
-    M, N, K = 300, 260, 65536
+@pytest.mark.parametrize("K", [65536, 65600])
+def test_long_contraction(ba, bw, K):
+    # 1024 and 1025 K-steps of fp32 accumulation, on wave tiles and on the 128 x 128 kernel, all outputs
+    M, N = 300, 260
     xc, xs, wc, wr = _inputs(M, N, K, ba, bw, seed=K + ba)
     Y = _gpu(xc, xs, wc, wr, ba, bw, K)
     args = (xc.numpy(), xs.double().numpy(), ba, wc.numpy(), wr.double().numpy(), bw, K)
@@ -280,12 +301,13 @@ def test_empty_operands_are_noops():
     assert Y.shape == (8, 0)
 
 
-# The two store paths of both GEMM kernels hold the same values: with N and ldy multiples of 4 the
+# The two store paths of the kernels hold the same values: with N and ldy multiples of 4 the
 # outputs are turned around in LDS before the stores, otherwise each lane stores its runs of four
 # columns directly.  Each output is the same arithmetic either way, so a layer written into rows of
 # N + 4 and into rows of N + 1 must agree bit for bit (large tiles, the 128 x 128 rows of a
-# partial last round, and a small grid; fp32 and the fused bias + GELU + bf16 epilogue).
-@pytest.mark.parametrize("M,N,K", [(4133, 8064, 192), (300, 132, 512)])
+# partial last round, a small grid on wave tiles, one on 128 x 128 tiles and one between the two (10 and 13 us);
+# fp32 and the fused bias + GELU + bf16 epilogue).
+@pytest.mark.parametrize("M,N,K", [(4133, 8064, 192), (300, 132, 512), (300, 132, 576), (201, 9216, 256)])
 @pytest.mark.parametrize("fused", [False, True])
 def test_store_paths_agree(M, N, K, fused):
     ba, bw = 4, 4
