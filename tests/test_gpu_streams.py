@@ -10,6 +10,7 @@ import pytest
 import torch
 
 import paper_2607_02461_amd as oq
+from paper_2607_02461_amd.launches import launches
 
 pytestmark = pytest.mark.gpu
 
@@ -92,10 +93,17 @@ def test_graph_capture_and_replay():
             assert torch.equal(a, b), f"replay {r}: {name} differ from the eager step"
 
 
-def test_graph_capture_of_split_layer():
-    # c1's layer split over K with a workspace (two kernels, no memset) captured with its
+def _assert_runs_split(call):
+    # which small layers run on the split kernel is known for 256 compute units
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert [r.kernel for r in launches(call)][-2:] == ["lut_gemm_kernel<4,4,true>", "lut_gemm_reduce"]
+
+
+# on 256 compute units the first has a workspace and runs on wave tiles, the second on the split kernel
+@pytest.mark.parametrize("M,N,K", [(256, 3072, 3072), (256, 5120, 5120)])
+def test_graph_capture_of_split_layer(M, N, K):
+    # a layer split over K with a workspace (two kernels, no memset) captured with its
     # quantizer, replayed on new inputs; every replay equals the eager step
-    K, M, N = 3072, 256, 3072
     plan, cb = oq.rpbh_plan(K, 128, 0), oq.lloydmax_codebook(4, K)
     W = _bf16(N, K, 19, scale=0.02)
     wc, wn = oq.quantize_weights_offline(plan, cb, W)
@@ -114,6 +122,8 @@ def test_graph_capture_of_split_layer():
 
     step()
     torch.cuda.synchronize()
+    if K == 5120:
+        _assert_runs_split(step)
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(s):
@@ -135,12 +145,11 @@ def test_graph_capture_of_split_layer():
             assert torch.equal(a, b), f"replay {r}: {name} differ from the eager step"
 
 
-def test_split_layers_on_two_streams_with_their_own_workspaces():
-    # two small layers split over K run at once on two streams, each with its own workspace,
-    # against the same calls one after the other on the default stream
-    K = 3072
+@pytest.mark.parametrize("K,shapes", [(3072, [(256, 3072), (64, 2000)]), (5120, [(256, 5120), (128, 9600)])])
+def test_split_layers_on_two_streams_with_their_own_workspaces(K, shapes):
+    # two small layers with workspaces (split over K at 5120, on wave tiles at 3072) run at once on two
+    # streams, each with its own workspace, against the same calls one after the other on the default stream
     plan, cb = oq.rpbh_plan(K, 128, 0), oq.lloydmax_codebook(4, K)
-    shapes = [(256, 3072), (64, 2000)]
     ops = []
     for i, (M, N) in enumerate(shapes):
         xc, xn = oq.rpbh_quantize_act(plan, cb, _bf16(M, K, 30 + i))
@@ -150,6 +159,9 @@ def test_split_layers_on_two_streams_with_their_own_workspaces():
         ops.append((xc, xn, wc, wn, torch.empty(n, dtype=torch.uint8, device=DEV)))
     ref = [oq.orbit_qlinear_ws(cb, xc, xn, cb, wc, wn, ws) for xc, xn, wc, wn, ws in ops]
     torch.cuda.synchronize()
+    if K == 5120:
+        for (xc, xn, wc, wn, ws), y in zip(ops, ref):
+            _assert_runs_split(lambda: oq.orbit_qlinear_ws(cb, xc, xn, cb, wc, wn, ws, out=y))
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     for s in streams:
         s.wait_stream(torch.cuda.current_stream())

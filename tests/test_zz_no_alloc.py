@@ -11,6 +11,7 @@ import torch
 import oracle
 import paper_2607_02461_amd as oq
 from paper_2607_02461_amd import workloads
+from paper_2607_02461_amd.launches import launches
 from tests.gpu_util import check_gemm, gemm_scale, qlinear_oracle_bf16
 
 pytestmark = pytest.mark.gpu
@@ -39,9 +40,12 @@ def _oracle_check(name, Y, host, ba, bw, K):
                gemm_scale(args[0], args[1], la, args[3], args[4], lw), K)
 
 
-def test_two_calls_in_a_row_match_the_workspace_layer():
+# K an odd multiple of 64: on the split kernel, through the scratch array; the others have a workspace
+# size too and run on wave tiles
+@pytest.mark.parametrize("more_k", [0, 64])
+def test_two_calls_in_a_row_match_the_workspace_layer(more_k):
     # c1's layer (256 x 3072 -> 3072, split over K), then a smaller split layer
-    for M, N, K, ba, bw, seed in ((256, 3072, 3072, 4, 4, 1), (40, 700, 1024, 4, 3, 2)):
+    for M, N, K, ba, bw, seed in ((256, 3072, 3072 + more_k, 4, 4, 1), (40, 700, 1024 + more_k, 4, 3, 2)):
         host, (cba, cbw), (xp, xs, wp, wr) = _operands(M, N, K, ba, bw, seed)
         n = oq.orbit_qlinear_workspace_size(M, N, K)
         assert 0 < n <= SCRATCH_BYTES
@@ -50,15 +54,19 @@ def test_two_calls_in_a_row_match_the_workspace_layer():
         out = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
         Y = oq.orbit_qlinear_noalloc(cba, xp, xs, cbw, wp, wr, out=out)
         torch.cuda.synchronize()
+        if more_k:
+            ran = launches(lambda: oq.orbit_qlinear_noalloc(cba, xp, xs, cbw, wp, wr, out=out))
+            assert [r.kernel for r in ran] == [f"lut_gemm_kernel<{ba},{bw},true>", "lut_gemm_reduce"]
         assert Y.data_ptr() == out.data_ptr()
         assert torch.equal(Y, Y_ws), f"M={M} N={N} K={K}: differs from orbit_qlinear_ws"
         _oracle_check(f"noalloc M={M} N={N} K={K} W{bw}A{ba}", Y, host, ba, bw, K)
 
 
-def test_fused_epilogue_and_unsplit_layers():
+@pytest.mark.parametrize("K", [2048, 2112])
+def test_fused_epilogue_and_unsplit_layers(K):
     # bias + GELU + bf16 output on a split layer; a layer that fills the device (no split, no
     # scratch) gives orbit_qlinear_ex's bits
-    M, N, K = 200, 390, 2048
+    M, N = 200, 390
     _, (cba, cbw), (xp, xs, wp, wr) = _operands(M, N, K, 4, 4, 11)
     bias = (torch.randn(N, device=DEV) * 0.1).to(torch.bfloat16)
     n = oq.orbit_qlinear_workspace_size(M, N, K)
