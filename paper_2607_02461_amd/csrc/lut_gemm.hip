@@ -31,14 +31,20 @@ constexpr int LDS_STRIDE = BK + 8;  // halves per tile row (padding against bank
 // c += b a^T for 16 rows of b and of a, 32 deep.  Written out so that the accumulator stays in its
 // registers: the compiler gives the intrinsic's result a fresh quad, and with 32 quads of
 // accumulators in 256 registers it then spills (2 to 22 registers; at 6-bit codes the large kernel ran
-// at 0.79 of the rate).  The compiler's hazard tracking does not look inside asm: the fragments come
-// from LDS loads (waited for by counter) and nothing but these MFMAs writes the accumulators between
-// their zeroing, which a barrier separates from the first use, and mfma_done().
+// at 0.79 of the rate).  The compiler's hazard tracking does not look inside asm, so the wait states are
+// ours: mfma_ready() stands between the accumulators' zeroing and their first MFMA, mfma_done() between
+// their last one and any other use, and nothing else writes them; the fragments come from LDS loads
+// (waited for by counter).  A test reads both distances off the built code.
 __device__ __forceinline__ void mfma16(floatx4& c, const bf16x8& b, const bf16x8& a) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(b), "v"(a));
 }
 
-// The wait states between the last MFMAs and the first other use of their results.
+// Two wait states between a VALU write of the accumulators and an MFMA that reads them.
+__device__ __forceinline__ void mfma_ready(floatx4 (&c)[4]) {
+    asm volatile("s_nop 1" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
+}
+
+// The wait states between the last MFMAs and the first other use of their results (eleven are needed).
 __device__ __forceinline__ void mfma_done(floatx4 (&c)[4]) {
     asm volatile("s_nop 15" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
 }
@@ -446,6 +452,8 @@ __global__ __launch_bounds__(512, 2) void lut_gemm_big(GemmParams p, int ntm, in
         for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mfma_ready(acc[i]);
 
     const int nk = p.K / BK2;
     const int astep = BK2 * BA / 8, bstep = BK2 * BW / 8;
