@@ -66,7 +66,7 @@ def source_digest():
     """Digest of the kernel sources; traffic counters taken from other sources are not used."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("rpbh_quantize.hip", "rpbh_quantize_row.hip", "lut_gemm.hip", "lut_decode.h"):
+    for f in ("rpbh_quantize.hip", "rpbh_quantize_row.hip", "lut_gemm.hip", "lut_gemm_wave.hip", "lut_decode.h"):
         with open(os.path.join(ROOT, "paper_2607_02461_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -215,11 +215,10 @@ def main():
             traffic = None
 
     # The layer's kernels, each launch timed alone with HIP events on the stream it runs on: the
-    # rows the 256x256 kernel takes and the rows the 128x128 kernel takes (split over K with the
-    # workspace, then the reduction), as orbit_qlinear_schedule names them
+    # rows the 256x256 kernel takes in full rounds and the rest, on whichever kernel runs them
     parts = [p for L in layers for p in gemm_parts(oq, L, args.part_reps)]
     dom = [p for p in parts if p["kernel"].startswith("lut_gemm_big")]
-    if not dom:   # a layer too small for the large kernel (c1): its split kernel pair dominates
+    if not dom:   # layers too small for the large kernel (c1)
         dom = parts
     dom_flops = sum(p["flops"] for p in dom)
     dom_ms = sum(p["ms"] for p in dom)
@@ -598,28 +597,28 @@ def _timed(fn, reps, before=None):
 
 def gemm_parts(oq, L, reps):
     """The kernel launches of one layer call, each timed alone: rows [0, rows_large) on the 256x256
-    kernel, then rows [rows_large, M) on the 128x128 kernel, split over K with the layer's workspace
-    and followed by the reduction when the schedule splits them.  Each part is the same launch the
-    whole call makes (the same rows, operands and split)."""
+    kernel, then rows [rows_large, M) on the kernel the library picks for them (when that is the one split
+    over K, with the layer's workspace and followed by the reduction).  Each part is the same launch the
+    whole call makes (the same rows, operands and split); its name is read off the call."""
+    from paper_2607_02461_amd.launches import launches
+
     lin = L["lin"]
     M, N, K = lin.M, lin.N, lin.K
-    rows, splits = oq.orbit_qlinear_schedule(M, N, K)
+    rows, _ = oq.orbit_qlinear_schedule(M, N, K)
     out = []
     for r0, r1 in ((0, rows), (rows, M)):
         if r1 <= r0:
             continue
         xc, xn, Y = L["xc"][r0:r1], L["xn"][r0:r1], L["Y"][r0:r1]
-        big = r0 == 0 and rows > 0
 
         def call():
             oq.orbit_qlinear_ws(L["cba"], xc, xn, L["cbw"], L["wc"], L["wn"], L["ws"], out=Y)
 
         mean, med, mn = _timed(call, reps)
         fl = 2.0 * (r1 - r0) * N * K
-        name = (f"lut_gemm_big<{lin.ba},{lin.bw}>" if big else
-                f"lut_gemm_kernel<{lin.ba},{lin.bw},{'true' if splits > 1 else 'false'}>"
-                + ("+lut_gemm_reduce" if splits > 1 else ""))
-        out.append({"linear": lin.name, "kernel": name, "rows": [r0, r1], "N": N, "K": K, "splits": 1 if big else splits,
+        ran = launches(call)
+        out.append({"linear": lin.name, "kernel": "+".join(r.kernel for r in ran), "rows": [r0, r1], "N": N, "K": K,
+                    "splits": ran[0].grid[2],
                     "flops": fl, "ms": mean, "ms_median": med, "ms_min": mn,
                     "tflops": fl / (mean * 1e-3) / 1e12, "frac": fl / (mean * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS})
     return out
@@ -631,6 +630,8 @@ def configs_sweep(oq, workloads, dev, reps):
     timestep 0), the image-DiT attention projections at W2A4 and W3A3 (c3), and the video recipe's
     W4A6 on the c4 up-projection.  Inputs smaller than the 256 MB Infinity Cache are evicted before
     each timed launch by writing a 512 MB buffer, so every launch streams its operands from HBM."""
+    from paper_2607_02461_amd.launches import launches
+
     flush = torch.empty(512 << 20, dtype=torch.uint8, device=dev)
 
     def evict():
@@ -669,9 +670,9 @@ def configs_sweep(oq, workloads, dev, reps):
         g = _timed(lambda: oq.orbit_qlinear_ws(cba, xc, xn, cbw, wc, wn, ws, out=Y), reps, evict)
         qb = quant_bytes(lin.M, lin.K, lin.ba)
         fl = 2.0 * lin.M * lin.N * lin.K
-        rows, splits = oq.orbit_qlinear_schedule(lin.M, lin.N, lin.K)
+        ran = launches(lambda: oq.orbit_qlinear_ws(cba, xc, xn, cbw, wc, wn, ws, out=Y))
         res.append({"workload": wname, "linear": lin.name, "M": lin.M, "K": lin.K, "N": lin.N,
-                    "bits": f"W{lin.bw}A{lin.ba}", "h": lin.h, "schedule": {"rows_large": rows, "splits": splits},
+                    "bits": f"W{lin.bw}A{lin.ba}", "h": lin.h, "kernels": [r.kernel for r in ran],
                     "quant_ms": q[0], "quant_ms_min": q[2], "quant_gbs": qb / (q[0] * 1e-3) / 1e9,
                     "quant_frac_of_hbm": qb / (q[0] * 1e-3) / 1e9 / HBM_PEAK_GBS,
                     "gemm_ms": g[0], "gemm_ms_min": g[2], "gemm_tflops": fl / (g[0] * 1e-3) / 1e12,

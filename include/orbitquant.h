@@ -259,9 +259,10 @@ orbit_status orbit_qlinear_ex(orbit_codebook cb_a, const uint8_t* x_codes, const
                               int64_t ldy, void* stream);
 
 /*
- * orbit_qlinear_workspace_size -- bytes of device workspace with which orbit_qlinear_ws splits
+ * orbit_qlinear_workspace_size -- bytes of device workspace with which orbit_qlinear_ws may split
  * the contraction over K for a layer of M x N outputs and K inputs on the current device; 0 when
- * it would not split.  A split pays where the grid of output tiles is too small to fill the
+ * it would not split.  The size holds for every bit width; where another kernel runs the rows faster
+ * without a workspace, the layer call leaves it untouched.  A split pays where the grid of output tiles is too small to fill the
  * device: a layer of few tokens, or the rows of a large layer's last, partly filled round of
  * tiles.  Each split contracts a contiguous range of K, so every compute unit stays busy.
  *
@@ -314,9 +315,9 @@ orbit_status orbit_qlinear_ws(orbit_codebook cb_a, const uint8_t* x_codes, const
  * bits), with the partial sums in a scratch array the library holds in device memory instead of a
  * caller workspace.  The call allocates nothing and calls no allocating routine.
  *   Limit: the scratch array is 32 MiB (33554432 bytes) per device, held by every device the
- *   library runs on until the process ends.  A layer whose split needs more
- *   (orbit_qlinear_workspace_size(M, N, K) > 32 MiB) returns ORBIT_EUNSUPPORTED; layers that do not
- *   split need none.
+ *   library runs on until the process ends.  A layer whose workspace size is larger
+ *   (orbit_qlinear_workspace_size(M, N, K) > 32 MiB) returns ORBIT_EUNSUPPORTED, at every bit width
+ *   and whichever kernel would run it; layers that do not split need none.
  *   Sharing: all calls on one device share its scratch array.  Calls that overlap in time on one
  *   device (on several streams, or from several threads without ordering) race on it and give
  *   undefined results; serialize them, e.g. on one stream.  The array keeps the last call's

@@ -347,8 +347,9 @@ def orbit_qlinear_ex(cb_a: Codebook, x_codes: torch.Tensor, x_norm: torch.Tensor
 
 
 def orbit_qlinear_workspace_size(M: int, N: int, K: int, device=None) -> int:
-    """Bytes of workspace with which orbit_qlinear_ws splits an M x N x K layer over K on
-    `device` (default: the current one); 0 when it would not split."""
+    """Bytes of workspace with which orbit_qlinear_ws may split an M x N x K layer over K on
+    `device` (default: the current one); 0 when it would not split.  The sizes alone decide it: at some
+    bit widths a kernel that needs no workspace is faster and runs instead."""
     n = ctypes.c_size_t(0)
     with torch.cuda.device(device if device is not None else torch.cuda.current_device()):
         _check("orbit_qlinear_workspace_size", lib().orbit_qlinear_workspace_size(M, N, K, ctypes.byref(n)))
@@ -357,7 +358,8 @@ def orbit_qlinear_workspace_size(M: int, N: int, K: int, device=None) -> int:
 
 def orbit_qlinear_schedule(M: int, N: int, K: int, device=None):
     """(rows_large, splits): rows [0, rows_large) of an M x N x K layer run on the 256 x 256 kernel,
-    the rest on the 128 x 128 kernel split `splits` ways over K when given a workspace."""
+    the rest on the 128 x 128 kernel split `splits` ways over K when given a workspace, or on another
+    kernel where that is faster (launches.launches lists what a call runs)."""
     rows, splits = _i64(0), _i32(1)
     with torch.cuda.device(device if device is not None else torch.cuda.current_device()):
         _check("orbit_qlinear_schedule", lib().orbit_qlinear_schedule(M, N, K, ctypes.byref(rows),
@@ -371,7 +373,7 @@ def orbit_qlinear_ws(cb_a: Codebook, x_codes: torch.Tensor, x_norm: torch.Tensor
                      out: torch.Tensor = None) -> torch.Tensor:
     """orbit_qlinear_ex with a caller workspace (a contiguous device tensor of any dtype, at least
     orbit_qlinear_workspace_size bytes, used on the current stream) that lets a small layer split
-    over K."""
+    over K where that is the fastest way."""
     return _qlinear("orbit_qlinear_ws", cb_a, x_codes, x_norm, cb_w, w_codes, w_norm, bias, gelu, out_dtype, out,
                     workspace)
 

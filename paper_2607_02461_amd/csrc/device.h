@@ -110,16 +110,18 @@ struct GemmParams {
     uint16_t lut_a[64];    // bf16 levels (2^ba used)
     uint16_t lut_w[16];    // bf16 levels (2^bw used)
     // K-split of the 128x128 kernel's rows (caller workspace): fp32 partial sums [splits][M][N]
-    // of the rows it runs, each split split_steps K-steps of 64; ws = null runs unsplit
+    // of the rows it runs, each split split_steps K-steps of 64; ws = null runs unsplit.  Rows that
+    // another kernel runs faster leave the workspace alone
     float* ws;
     int splits, split_steps;
 };
 
 hipError_t launch_lut_gemm(const GemmParams& p, int ba, int bw, int cus, hipStream_t stream);
-// Rows [0, m_big) of an M x N layer run on the 256x256 kernel, the rest on the 128x128 kernel
+// Rows [0, m_big) of an M x N layer run on the 256x256 kernel in rounds of a tile per compute unit, the
+// rest on whichever kernel is estimated the fastest for them
 int64_t lut_gemm_big_rows(int64_t M, int64_t N, int64_t K, int cus);
-// K-splits of the 128x128 kernel on M x N outputs when a workspace is given (1: none), and the
-// K-steps per split (the last split may have fewer)
+// K-splits of the 128x128 kernel on M x N outputs, should it run them with a workspace (1: none), and
+// the K-steps per split (the last split may have fewer)
 int lut_gemm_small_splits(int64_t M, int64_t N, int64_t K, int cus, int* split_steps);
 
 // The same layer on one workgroup per output tile of 16 mt x 16 nt, its contraction split over the

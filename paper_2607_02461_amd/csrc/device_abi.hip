@@ -356,7 +356,7 @@ orbit_status orbit_qlinear_ws(orbit_codebook cb_a, const uint8_t* x_codes, const
     g.gelu = act == ORBIT_ACT_GELU;
     g.out_bf16 = out_dtype == ORBIT_OUT_BF16;
     g.vec4 = aligned(Y, 4 * ysize) && ldy % 4 == 0 && aligned(w_norm, 8) && (!bias || aligned(bias, 8));
-    // K-split of the rows the 128x128 kernel runs, when the caller's workspace holds the partial sums
+    // K-split of the rows left to the 128x128 kernel, when the caller's workspace holds the partial sums
     const int64_t m_small = M - lut_gemm_big_rows(M, N, K, info.cus);
     g.splits = m_small > 0 ? lut_gemm_small_splits(m_small, N, K, info.cus, &g.split_steps) : 1;
     if (g.splits > 1 && workspace && aligned(workspace, 16) &&
@@ -507,8 +507,8 @@ orbit_status orbit_qlinear_noalloc(orbit_codebook cb_a, const uint8_t* x_codes, 
         if (st != ORBIT_OK) return st;
         if (need > kScratchBytes)
             return fail(ORBIT_EUNSUPPORTED,
-                        "orbit_qlinear_noalloc: a %lld x %lld x %lld layer splits over K into %zu bytes of partial sums, "
-                        "above the %zu-byte scratch limit (use orbit_qlinear_ws with a workspace of that size)",
+                        "orbit_qlinear_noalloc: the workspace size of a %lld x %lld x %lld layer is %zu bytes, above the "
+                        "%zu-byte scratch limit (use orbit_qlinear_ws with a workspace of that size)",
                         (long long)M, (long long)N, (long long)K, need, kScratchBytes);
     }
     void* ws = nullptr;

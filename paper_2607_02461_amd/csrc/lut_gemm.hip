@@ -79,7 +79,7 @@ __device__ __forceinline__ void load_codes32(__amdgpu_buffer_rsrc_t buf, uint32_
 // fewer) and stores its raw sums to p.ws[z][M][N]; lut_gemm_reduce applies the epilogue.
 //
 // 128x128 block tiles, K-step 64, four waves of 64x64.  This kernel serves grids too small for the
-// 256x256 kernel (often one workgroup per compute unit, so one wave per SIMD), where each
+// 256x256 kernel where wave tiles are not faster (often one workgroup per compute unit, so one wave per SIMD), where each
 // workgroup's time is its chain of K-steps: it is pipelined like the large kernel.  The block
 // tile's codes are decoded once per K-step into a double-buffered bf16 tile in LDS (74 KB); while
 // the matrix cores work on step s, each wave decodes step s+1 into the other stage (groups 0-1,
@@ -850,9 +850,9 @@ int64_t lut_gemm_big_rows(int64_t M, int64_t N, int64_t K, int cus) {
     // Wave quantization: the large kernel runs one tile per compute unit at a time, so a last round
     // that is only partly full costs as long as a full one (c4's down-projection: 2600 tiles, an
     // eleventh round of 40).  When that pays, the large kernel takes the tile rows that fill its
-    // full rounds and the 128x128 kernel the rest.  A round of those does a quarter of a large
-    // tile's work per workgroup but, with one workgroup per compute unit, is latency-bound and
-    // takes 0.6-0.8 of a large round (c4's down-projection: 4.61 -> 4.53 ms; the up-projection,
+    // full rounds and another kernel the rest, priced here as 128x128 tiles (fastest_kernel may find a
+    // faster one).  A round of those does a quarter of a large tile's work per workgroup but, with
+    // one workgroup per compute unit, is latency-bound and takes 0.6-0.8 of a large round (c4's down-projection: 4.61 -> 4.53 ms; the up-projection,
     // whose last round is 42% full, is left alone).
     const int64_t rows_big = (tiles / cus) * cus / ntn;
     if (rows_big > 0 && rows_big < ntm) {
