@@ -304,25 +304,50 @@ hipError_t launch_one_token(const RtnLinearParams& p, int cus, hipStream_t strea
     return launch_linear<1, 2>(p, 6, cus, stream);
 }
 
-// Several tokens: two or four a pass over the weights (at 150 registers, three workgroups per compute unit).
-// One row per group where that grid is resident at once, as the latencies decide there (4 x 3072 -> 12288:
-// 10.1 us, two rows 11.1; 2 x 3072 -> 9216: 7.2 and 7.7), two where workgroups queue (8 x 3072 -> 18432:
-// 23.9 -> 22.5; 101 x 5120 -> 40000: 775 -> 687).  Four tokens a pass except where
-//   - the last pass would be half empty: 5 and 6 tokens (3072 -> 18432: 21.4 us two at a time, 23.4 four);
-//   - two at a time still fit twice per compute unit (4 x 5120 -> 2048: 7.0 us, 9.4);
-//   - four tokens leave LDS for fewer than three workgroups (16 x 16384 -> 18432: 282 us, 335).
+// Several tokens: two or four a pass over the weights, one row per group of lanes or two, by an estimate in
+// microseconds fitted to 900 calls timed all four ways (2 to 100 tokens, N 512 .. 80000, K 512 .. 8192, 256
+// compute units): `base`, and per 1024 inputs `load` for each round of resident workgroups and `work` for
+// each block of 16 rows on the busiest compute unit.  The choice costs 1% over the fastest of the four on
+// average.  Three forms are left out beforehand:
+//   - two rows per group where the grid of one row is resident at once, as latencies decide there (4 x 3072 ->
+//     12288: 10.1 us, two rows 11.1; 9 x 5120 -> 1993: 10.0 and 10.6);
+//   - one row and two tokens where workgroups queue and a call has several passes, or LDS holds fewer than three
+//     workgroups (10 x 5120 -> 3182: 16.8 us, two rows 10.8; 13 x 15296 -> 1264: 36.7 and 27.5).  Two tokens, a
+//     single pass, go by which form spreads the rows more evenly (2 x 5120 -> 35225: 24.1 us, two rows
+//     27.1; -> 37000: 28.9 and 27.4);
+//   - four tokens where LDS holds one workgroup of them (16 x 16384 -> 18432: 335 us, two tokens 282).
+struct RtnWay {
+    int mt, rows, per_cu;     // per_cu: workgroups that a compute unit's registers hold
+    double base, load, work;
+    hipError_t (*launch)(const RtnLinearParams&, int, int, hipStream_t);
+};
+constexpr RtnWay kRtnWays[] = {{2, 1, 3, 2.85, 0.35, 0.343, launch_linear<2, 1>},
+                               {2, 2, 3, 2.65, 0.40, 0.348, launch_linear<2, 2>},
+                               {4, 1, 4, 3.00, 0.62, 0.527, launch_linear<4, 1>},
+                               {4, 2, 3, 3.00, 0.62, 0.510, launch_linear<4, 2>}};
+
 hipError_t launch_tokens(const RtnLinearParams& p, int cus, hipStream_t stream) {
-    hipError_t e = raise_rtn_lds<2, 1>(p.K);
-    if (e == hipSuccess) e = raise_rtn_lds<4, 1>(p.K);
-    if (e != hipSuccess) return e;
-    const int64_t blocks = rtn_blocks(p.N, 1), wgs2 = blocks * ((p.M + 1) / 2), wgs4 = blocks * ((p.M + 3) / 4);
-    const bool four = p.M > 2 && p.M != 5 && p.M != 6;
-    const int fit2 = resident_blocks((const void*)adaln_int4_linear_kernel<2, 1>, 256, rtn_lds(2, p.K));
-    const int fit4 = resident_blocks((const void*)adaln_int4_linear_kernel<4, 1>, 256, rtn_lds(4, p.K));
-    if (wgs2 <= (int64_t)(four ? std::min(2, fit2) : fit2) * cus) return launch_linear<2, 1>(p, 3, cus, stream);
-    if (four && wgs4 <= (int64_t)fit4 * cus) return launch_linear<4, 1>(p, 4, cus, stream);
-    if (four && 3 * rtn_lds(4, p.K) <= 160 * 1024) return launch_linear<4, 2>(p, 3, cus, stream);
-    return launch_linear<2, 2>(p, 3, cus, stream);
+    const RtnWay* fastest = nullptr;
+    double best = 0.0;
+    bool once = false;  // the grid of one row per group is resident at once (each pair's first entry sets it)
+    for (const RtnWay& w : kRtnWays) {
+        const RtnGrid g = rtn_grid(p.N, w.rows, w.per_cu, cus);
+        const int64_t workgroups = g.workgroups * ((p.M + w.mt - 1) / w.mt);
+        const int64_t fit = (int64_t)(160 * 1024 / rtn_lds(w.mt, p.K));
+        const int64_t resident = std::min<int64_t>(w.per_cu, fit) * cus;
+        if (w.rows == 1) once = g.rounds == 1 && workgroups <= resident;
+        if (w.mt == 4 && (p.M == 2 || fit < 2)) continue;
+        if (w.rows == 2 && once) continue;
+        if (w.mt == 2 && w.rows == 1 && !once && (p.M > 2 || fit < 3)) continue;
+        const double t = w.base + std::max(p.K, 32 * kRtnLanes) / 1024.0 * (double)g.rounds *
+                                      (w.load * (double)((workgroups + resident - 1) / resident) +
+                                       w.work * w.rows * (double)((workgroups + cus - 1) / cus));
+        if (!fastest || t < best) {
+            fastest = &w;
+            best = t;
+        }
+    }
+    return fastest->launch(p, fastest->per_cu, cus, stream);
 }
 
 }  // namespace

@@ -93,8 +93,13 @@ def test_linear_strided_input_and_padded_output():
 # whichever way a call goes, every token's outputs are the bits of a call of its own.
 @pytest.mark.parametrize("M,N,K,kernel", [(4, 1000, 3072, "<2,1>"), (2, 9001, 1600, "<2,1>"), (3, 12289, 1088, "<4,1>"),
                                           (7, 8001, 1088, "<4,1>"), (2, 18433, 1088, "<2,2>"), (5, 9217, 64, "<2,2>"),
-                                          (6, 9217, 1600, "<2,2>"), (3, 18449, 128, "<4,2>"), (8, 9233, 1088, "<4,2>"),
-                                          (9, 9233, 192, "<4,2>"), (4, 9001, 16384, "<2,2>")])
+                                          (6, 9217, 1600, "<2,2>"), (3, 18449, 128, "<2,2>"), (8, 9233, 1088, "<4,2>"),
+                                          (9, 9233, 192, "<2,2>"), (4, 9001, 16384, "<2,2>"),
+                                          # one row per group although workgroups queue; rows spread more evenly so
+                                          (2, 35225, 1088, "<2,1>"), (2, 37000, 1088, "<2,2>"),
+                                          # several passes on one resident grid; a few workgroups more
+                                          (9, 1993, 5120, "<2,1>"), (10, 3182, 5120, "<2,2>"), (9, 18433, 1088, "<4,2>"),
+                                          (11, 12305, 192, "<4,2>")])
 def test_tokens_of_a_pass(M, N, K, kernel):
     W = _weights(N, K, seed=M + N + K)
     q, s = oq.adaln_int4_quantize_weights(W)

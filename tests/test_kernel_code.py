@@ -39,3 +39,13 @@ def test_large_kernel_keeps_the_wait_states_of_its_mfmas():
     for name, code in kernels.items():
         assert sum(i[0] == "v_mfma_f32_16x16x32_bf16" for i in code) >= 4 * 64, name
         assert mfma_hazards(code) == [], name
+
+
+def test_adaln_kernel_fits_the_workgroups_its_launcher_counts_on():
+    # workgroups of four waves on a compute unit, one wave of each per SIMD of 512 registers
+    kernels = {n: k for n, k in kernel_metadata().items() if n.startswith("adaln_int4_linear_kernel<")}
+    fit = {"<1,1>": 6, "<1,2>": 6, "<2,1>": 3, "<2,2>": 3, "<4,1>": 4, "<4,2>": 3}
+    assert {n[n.index("<"):] for n in kernels} == set(fit)
+    for name, k in kernels.items():
+        assert k[".vgpr_spill_count"] == 0, name
+        assert 512 // ((k[".vgpr_count"] + 7) // 8 * 8) == fit[name[name.index("<"):]], f"{name} takes {k['.vgpr_count']}"
