@@ -740,10 +740,11 @@ __global__ __launch_bounds__(256) void lut_gemm_reduce(GemmParams p, int splits)
 
 // The kernel for rows that do not fill the device with large tiles, by an estimate of each one's
 // microseconds.  Fitted to 1600 layers timed on all three (M 1 .. 8000, N 96 .. 18432, K 256 .. 16384, every
-// bit pair, 256 compute units): nine in ten estimates within 14%, and where rows are not stored in
-// vectors (N or ldy not a multiple of 4) four in five within 20%.  The choice costs 0.1% over the
-// fastest kernel on average, 19% at worst; 9 of 2986 calls (each layer with a workspace and without) are
-// over 3% slower than on 128 x 128 tiles, the worst 13%.  A tie stays on the 128 x 128 kernel.
+// bit pair, 256 compute units): nine in ten estimates within 13%, and where rows are not stored in
+// vectors (N no multiple of 4) four in five within 15%.  The row stride of Y does not enter, so that a
+// layer's outputs are the same bits wherever they are written.  The choice costs 0.1% over the fastest
+// kernel on average, 25% at worst; 6 of 2986 calls (each layer with a workspace and without) are over 3%
+// slower than on 128 x 128 tiles, the worst 9%.  A tie stays on the 128 x 128 kernel.
 enum class Kernel { kSmall, kWave, kLarge };
 
 Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int splits, int split_steps, int cus) {
@@ -759,11 +760,13 @@ Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int split
     // element add 9 us for each further workgroup.
     const int64_t wgs = tiles(BM, BN) * splits, k = (wgs + cus - 1) / cus;
     const double step = k == 1 ? 0.58 : k == 2 ? 1.03 : k == 3 ? 1.64 : k == 4 ? 2.13 : 0.48 * (double)wgs / cus;
+    // (beside another workgroup's MFMAs the dearer decodes hide better)
+    const double fs = k > 1 ? 1.0 + 0.85 * (f - 1.0) : f;
     const double more = (double)(k - 1), sums = (double)splits * (double)M * (double)N * 8e-6;  // MB
     double best;
-    if (splits > 1 && vectors) best = 6.4 + 0.45 * more + step * f * split_steps + 0.23 * splits + 0.19 * sums;
-    else if (splits > 1) best = 7.3 + 0.9 * step * f * split_steps + 0.49 * splits + 0.6 * sums;
-    else best = (vectors ? 6.4 + 0.45 * more : 9.5 + 9.0 * more) + step * f * steps;
+    if (splits > 1 && vectors) best = 6.4 + 0.45 * more + step * fs * split_steps + 0.23 * splits + 0.19 * sums;
+    else if (splits > 1) best = 7.3 + 0.9 * step * fs * split_steps + 0.49 * splits + 0.6 * sums;
+    else best = (vectors ? 6.4 + 0.45 * more : 9.5 + 9.0 * more) + step * fs * steps;
     Kernel kernel = Kernel::kSmall;
     // 256 x 256, one round: 1.27 us per K-step while up to 0.6 of the compute units have a tile, 1.52 us
     // when all do (the clock falls).  4429 x 3072 x 3072 W3A3: 85 us against 129 on 128 x 128 tiles;
@@ -778,13 +781,15 @@ Kernel fastest_kernel(int64_t M, int64_t N, int64_t K, int ba, int bw, int split
         }
     }
     // wave tiles, whole chunks of 128 only: the busiest compute unit's tiles, 1.2 us for a 64 x 64 one and
-    // 0.34 us for each of its chunks, others 0.3 in proportion to their decode.  (Without the cost of a
-    // tile, short contractions went here wrongly: 1319 x 5120 x 640 W4A2 27.4 us, 20.2 on 128 x 128 tiles.)
+    // 0.34 us for each of its chunks (4-bit codes decode a little faster than 2-bit ones there), others 0.3
+    // in proportion to their decode.  (Without the cost of a tile, short contractions went here wrongly:
+    // 1319 x 5120 x 640 W4A2 27.4 us, 20.2 on 128 x 128 tiles.)
     if (K % 128 == 0 && (M + 15) / 16 <= 65535) {
         const WaveTile w = lut_gemm_wave_tile(M, N, K, cus);
         const double per_cu = (double)((tiles(16 * w.mt, 16 * w.nt) + cus - 1) / cus) * (w.mt + w.nt) / 8.0;
         const bool whole = w.mt == 4 && w.nt == 4;
-        const double t = 3.3 + per_cu * ((whole ? 1.2 : 0.0) + (whole ? 0.34 : 0.3) * f * (double)(K / 128));
+        const double fw = whole ? f - 0.025 * ((ba == 4) + (bw == 4)) : f;
+        const double t = 3.3 + per_cu * ((whole ? 1.2 : 0.0) + (whole ? 0.34 : 0.3) * fw * (double)(K / 128));
         if (t < best) kernel = Kernel::kWave;
     }
     return kernel;

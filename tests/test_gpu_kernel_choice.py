@@ -34,6 +34,9 @@ def kernels(M, N, K, ba, bw, workspace=False):
     (1, 223, 13824, 4, 4, True, "lut_gemm_wave"),          # 33, 10
     # 6-bit codes on 64 x 64 wave tiles against the split kernel
     (365, 9584, 3072, 6, 4, True, "lut_gemm_kernel"),      # 54.2, 59.7
+    (271, 9216, 12288, 6, 3, True, "lut_gemm_kernel"),     # 138, 156
+    # and 4-bit ones
+    (1388, 3072, 5120, 4, 4, True, "lut_gemm_wave"),       # 79.9, 68.8
     # K no multiple of 128: never on wave tiles
     (1, 3072, 3136, 4, 4, False, "lut_gemm_kernel"),
     # one partial round of large tiles
